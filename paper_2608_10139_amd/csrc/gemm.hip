@@ -14,7 +14,8 @@
 //
 // M (tokens in the chunk) is read from device memory; the grid is persistent
 // (one workgroup per CU) and walks the tiles, so an empty chunk costs one
-// launch and no work.
+// launch and no work.  Where M leaves 256 x 256 tiles too few for the chip the
+// same launch takes 128 x 128 or 64 x 64 ones (tile_path).
 //
 // fp32 path: a plain 64 x 64 LDS-tiled FMA kernel with the same row mapping
 // and epilogues, used for fp32 models.
@@ -44,14 +45,6 @@ static int num_cus() {
 }
 
 
-__device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d) {
-  uint2 p;
-  p.x = f2bf(a) | (static_cast<uint32_t>(f2bf(b)) << 16);
-  p.y = f2bf(c) | (static_cast<uint32_t>(f2bf(d)) << 16);
-  return p;
-}
-
-__device__ __forceinline__ float silu(float g) { return g / (1.0f + expf(-g)); }
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
 // Row of the q or k weight that produces GEMM column c of that section.
@@ -176,6 +169,117 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// ---- epilogues of one 8-column piece (columns c .. c + 7 of row m; `in`: m < M)
+// x += acc in place; with a following norm also h = x * g and, per 64
+// columns (eight neighbouring lanes, in a fixed butterfly order), the sum of
+// x^2.  g0, g1: the norm's gains of the columns.
+template <int EPI, bool H>
+__device__ __forceinline__ void resid_piece(const GemmArgs& a, float4 x0, float4 x1, const float4& s0,
+                                            const float4& s1, const float4& g0, const float4& g1, int64_t m, int c,
+                                            bool in, int pc, bool norm, uint16_t* hout) {
+  x0.x += s0.x; x0.y += s0.y; x0.z += s0.z; x0.w += s0.w;
+  x1.x += s1.x; x1.y += s1.y; x1.z += s1.z; x1.w += s1.w;
+  float ssq = 0.f;
+  if (in) {
+    float* xr = a.x + m * a.ldc + c;
+    *reinterpret_cast<float4*>(xr) = x0;
+    *reinterpret_cast<float4*>(xr + 4) = x1;
+    if (norm) {
+      const float hv[8] = {x0.x * g0.x, x0.y * g0.y, x0.z * g0.z, x0.w * g0.w,
+                           x1.x * g1.x, x1.y * g1.y, x1.z * g1.z, x1.w * g1.w};
+      *reinterpret_cast<uint4*>(hout + m * a.ldc + c) = pack8<H>(hv);
+    }
+    ssq = ((x0.x * x0.x + x0.y * x0.y) + (x0.z * x0.z + x0.w * x0.w)) +
+          ((x1.x * x1.x + x1.y * x1.y) + (x1.z * x1.z + x1.w * x1.w));
+  }
+  if (norm) {
+    ssq += dpp_f32<0xB1>(ssq);    // quad_perm [1,0,3,2]: lane ^ 1
+    ssq += dpp_f32<0x4E>(ssq);    // quad_perm [2,3,0,1]: lane ^ 2
+    ssq += dpp_f32<0x141>(ssq);   // row_half_mirror: the other quad of the eight, whose lanes agree
+    if ((pc & 7) == 0 && in) a.ssp[m * a.n_part + (c >> 6)] = ssq;
+  }
+}
+
+// Row maximum over each 64 columns: the lane's 8 columns in increasing order
+// (a strictly greater value replaces), then eight lanes in a butterfly that
+// keeps the lower column on ties.
+__device__ __forceinline__ void argmax_piece(const GemmArgs& a, const float4& s0, const float4& s1, int64_t m,
+                                             int col, bool in, int pc) {
+  const float v8[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+  float v = v8[0];
+  int c = col;
+#pragma unroll
+  for (int e = 1; e < 8; ++e)
+    if (v8[e] > v) {
+      v = v8[e];
+      c = col + e;
+    }
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) {
+    const float ov = __shfl_xor(v, o);
+    const int oc = __shfl_xor(c, o);
+    if (ov > v || (ov == v && oc < c)) {
+      v = ov;
+      c = oc;
+    }
+  }
+  if ((pc & 7) == 0 && in) static_cast<int2*>(a.C)[m * a.ldc + (col >> 6)] = make_int2(__float_as_int(v), c);
+}
+
+template <int EPI, bool H>
+__device__ __forceinline__ void store_piece(const GemmArgs& a, const float4& s0, const float4& s1, int64_t m, int c) {
+  if (EPI == EPI_STORE_F32) {
+    float* cr = static_cast<float*>(a.C) + m * a.ldc + c;
+    *reinterpret_cast<float4*>(cr) = s0;
+    *reinterpret_cast<float4*>(cr + 4) = s1;
+  } else {
+    const float v8[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+    *reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.C) + m * a.ldc + c) = pack8<H>(v8);
+  }
+}
+
+// SwiGLU and rotary pairs: pieces q and q + 4 of the 64-column half that
+// starts at column nh (gate and up; lower and upper half dims), scaled by the
+// row's RMSNorm scale rs.  rv: rotary frequencies of a head's lower dims.
+template <int EPI, bool H>
+__device__ __forceinline__ void pair_piece(const GemmArgs& a, const float4& l0, const float4& l1, const float4& u0,
+                                           const float4& u1, float rs, int nh, int q, int64_t m, int32_t position,
+                                           const float* rv) {
+  const float lo[8] = {l0.x * rs, l0.y * rs, l0.z * rs, l0.w * rs, l1.x * rs, l1.y * rs, l1.z * rs, l1.w * rs};
+  const float up[8] = {u0.x * rs, u0.y * rs, u0.z * rs, u0.w * rs, u1.x * rs, u1.y * rs, u1.z * rs, u1.w * rs};
+  uint16_t* crow = static_cast<uint16_t*>(a.C) + m * a.ldc;
+  if (EPI == EPI_SWIGLU) {
+    float o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = silu_fast(lo[e]) * up[e];
+    *reinterpret_cast<uint4*>(crow + (nh >> 1) + 8 * q) = pack8<H>(o);
+  } else if (nh >= a.n_q + a.n_kv) {   // v: natural order
+    *reinterpret_cast<uint4*>(crow + nh + 8 * q) = pack8h(lo);
+    *reinterpret_cast<uint4*>(crow + nh + 32 + 8 * q) = pack8h(up);
+  } else {
+    const int sbase = nh < a.n_q ? 0 : a.n_q;
+    // 64- or 128-dim heads: column nh of a section is the head's own (hh 0) or second 64-column half
+    const int hh = a.hd == 128 ? ((nh - sbase) >> 6) & 1 : 0, half = a.hd >> 1;
+    const float pos = static_cast<float>(position);
+    const float4 f0 = *reinterpret_cast<const float4*>(rv + hh * 32 + 8 * q);
+    const float4 f1 = *reinterpret_cast<const float4*>(rv + hh * 32 + 8 * q + 4);
+    const float fr[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
+    float ol[8], ou[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      // angle pos * theta^(-2i/hd), in revolutions (hardware sin/cos take revolutions)
+      const float rev = pos * fr[e];
+      const float frac = rev - floorf(rev);
+      const float cs = __builtin_amdgcn_cosf(frac), sn = __builtin_amdgcn_sinf(frac);
+      ol[e] = lo[e] * cs - up[e] * sn;   // lower half dim
+      ou[e] = up[e] * cs + lo[e] * sn;   // upper half dim
+    }
+    uint16_t* dst = crow + nh - hh * 32 + 8 * q;
+    *reinterpret_cast<uint4*>(dst) = pack8h(ol);
+    *reinterpret_cast<uint4*>(dst + half) = pack8h(ou);
+  }
+}
+
 // `rl` holds the tile's row scales (QKV, SwiGLU) or the following norm's gain
 // for the tile's columns (residual), `pl` the tile's positions and `rv` the
 // rotary frequencies of a head's lower-half dims (revolutions per position),
@@ -185,7 +289,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 template <int EPI, bool H, typename Prefetch>
 __device__ __forceinline__ void epilogue_bf16(const GemmArgs& a, f32x16 (&acc)[4][4], int64_t m0, int n0,
                                               int64_t M, int wm, int wn, int lane, float4* slice, const float* rl,
-                                              const int32_t* pl, const float* rv, Prefetch prefetch) {
+                                              const int32_t* pl, const float* rv, int64_t tok0, Prefetch prefetch) {
   const int l32 = lane & 31, hi = lane >> 5;
   const int nw = n0 + wn * 128;   // first GEMM column of the wave's sub-tile
   const int pc = lane & 15;       // piece (8 columns) of a row this lane reads back
@@ -210,7 +314,6 @@ __device__ __forceinline__ void epilogue_bf16(const GemmArgs& a, f32x16 (&acc)[4
       // rows' residuals of this lane are read before any is used.
       const bool norm = a.gnext != nullptr;
       uint16_t* hout = static_cast<uint16_t*>(a.hout);
-      const int64_t tok0 = EPI == EPI_RESID_EMB ? a.x_tok_desc[D_TOK_BEGIN] : 0;
       const int col = nw + 8 * pc;
       float4 xv[8][2];
 #pragma unroll
@@ -248,131 +351,34 @@ __device__ __forceinline__ void epilogue_bf16(const GemmArgs& a, f32x16 (&acc)[4
       for (int rr = 0; rr < 8; ++rr) {
         const int r = 4 * rr + pr;
         const int64_t m = m0 + row0 + r;
-        const float4 s0 = slice[eslot(r, 2 * pc)], s1 = slice[eslot(r, 2 * pc + 1)];
         float4 x0 = xv[rr][0], x1 = xv[rr][1];
-        x0.x += s0.x; x0.y += s0.y; x0.z += s0.z; x0.w += s0.w;
-        x1.x += s1.x; x1.y += s1.y; x1.z += s1.z; x1.w += s1.w;
-        float ssq = 0.f;
-        if (m < M) {
-          float* xr = a.x + m * a.ldc + col;
-          *reinterpret_cast<float4*>(xr) = x0;
-          *reinterpret_cast<float4*>(xr + 4) = x1;
-          if (norm) {
-            const float hv[8] = {x0.x * g0.x, x0.y * g0.y, x0.z * g0.z, x0.w * g0.w,
-                                 x1.x * g1.x, x1.y * g1.y, x1.z * g1.z, x1.w * g1.w};
-            *reinterpret_cast<uint4*>(hout + m * a.ldc + col) = pack8<H>(hv);
-          }
-          ssq = ((x0.x * x0.x + x0.y * x0.y) + (x0.z * x0.z + x0.w * x0.w)) +
-                ((x1.x * x1.x + x1.y * x1.y) + (x1.z * x1.z + x1.w * x1.w));
-        }
-        if (norm) {
-          ssq += dpp_f32<0xB1>(ssq);    // quad_perm [1,0,3,2]: lane ^ 1
-          ssq += dpp_f32<0x4E>(ssq);    // quad_perm [2,3,0,1]: lane ^ 2
-          ssq += dpp_f32<0x141>(ssq);   // row_half_mirror: the other quad of the eight, whose lanes agree
-          if ((pc & 7) == 0 && m < M) a.ssp[m * a.n_part + ((nw >> 6) + (pc >> 3))] = ssq;
-        }
+        const float4 s0 = slice[eslot(r, 2 * pc)], s1 = slice[eslot(r, 2 * pc + 1)];
+        resid_piece<EPI, H>(a, x0, x1, s0, s1, g0, g1, m, col, m < M, pc, norm, hout);
       }
-    } else if (EPI == EPI_ARGMAX) {
-      // row maxima over each 64-column half: the lane's 8 columns in
-      // increasing order (a strictly greater value replaces), then the eight
-      // lanes of the half in a butterfly that keeps the lower column on ties
-      int2* P = static_cast<int2*>(a.C);
+    } else if (EPI != EPI_SWIGLU && EPI != EPI_QKV_ROPE) {
 #pragma unroll
       for (int rr = 0; rr < 8; ++rr) {
         const int r = 4 * rr + pr;
         const int64_t m = m0 + row0 + r;
         const float4 s0 = slice[eslot(r, 2 * pc)], s1 = slice[eslot(r, 2 * pc + 1)];
-        const float v8[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
-        float v = v8[0];
-        int c = nw + 8 * pc;
-#pragma unroll
-        for (int e = 1; e < 8; ++e)
-          if (v8[e] > v) {
-            v = v8[e];
-            c = nw + 8 * pc + e;
-          }
-#pragma unroll
-        for (int o = 1; o < 8; o <<= 1) {
-          const float ov = __shfl_xor(v, o);
-          const int oc = __shfl_xor(c, o);
-          if (ov > v || (ov == v && oc < c)) {
-            v = ov;
-            c = oc;
-          }
-        }
-        if ((pc & 7) == 0 && m < M) P[m * a.ldc + ((nw >> 6) + (pc >> 3))] = make_int2(__float_as_int(v), c);
-      }
-    } else if (EPI == EPI_STORE_F32) {
-      float* C = static_cast<float*>(a.C);
-#pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        const int r = 4 * rr + pr;
-        const int64_t m = m0 + row0 + r;
-        if (m < M) {
-          float* cr = C + m * a.ldc + nw + 8 * pc;
-          *reinterpret_cast<float4*>(cr) = slice[eslot(r, 2 * pc)];
-          *reinterpret_cast<float4*>(cr + 4) = slice[eslot(r, 2 * pc + 1)];
-        }
-      }
-    } else if (EPI == EPI_STORE_ACT) {
-      uint16_t* C = static_cast<uint16_t*>(a.C);
-#pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        const int r = 4 * rr + pr;
-        const int64_t m = m0 + row0 + r;
-        const float4 s0 = slice[eslot(r, 2 * pc)], s1 = slice[eslot(r, 2 * pc + 1)];
-        const float v8[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
-        if (m < M) *reinterpret_cast<uint4*>(C + m * a.ldc + nw + 8 * pc) = pack8<H>(v8);
+        if (EPI == EPI_ARGMAX)
+          argmax_piece(a, s0, s1, m, nw + 8 * pc, m < M, pc);
+        else if (m < M)
+          store_piece<EPI, H>(a, s0, s1, m, nw + 8 * pc);
       }
     } else {
-      // SwiGLU and rotary pairs: pieces q (0..3) and q + 4 of one 64-column
-      // half h; lane piece pc -> (h, q) = (pc / 8, pc % 4) on rows of parity
-      // pc / 4 % 2: 32 rows x 2 halves x 4 pairs = 256 pair-pieces, 4 per lane
-      uint16_t* C = static_cast<uint16_t*>(a.C);
+      // pieces q (0..3) and q + 4 of one 64-column half h; lane piece pc ->
+      // (h, q) = (pc / 8, pc % 4) on rows of parity pc / 4 % 2: 32 rows x 2
+      // halves x 4 pairs = 256 pair-pieces, 4 per lane
       const int h = pc >> 3, q = pc & 3, rp = (pc >> 2) & 1;
-      const int nh = nw + 64 * h;
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) {
         const int r = 8 * rr + 2 * pr + rp;
         const int tr = row0 + r;
-        const int64_t m = m0 + tr;
         const float rs = a.rs ? rl[tr] : 1.f;   // RMSNorm row scale
         const float4 l0 = slice[eslot(r, 16 * h + 2 * q)], l1 = slice[eslot(r, 16 * h + 2 * q + 1)];
         const float4 u0 = slice[eslot(r, 16 * h + 2 * q + 8)], u1 = slice[eslot(r, 16 * h + 2 * q + 9)];
-        const float lo[8] = {l0.x * rs, l0.y * rs, l0.z * rs, l0.w * rs, l1.x * rs, l1.y * rs, l1.z * rs, l1.w * rs};
-        const float up[8] = {u0.x * rs, u0.y * rs, u0.z * rs, u0.w * rs, u1.x * rs, u1.y * rs, u1.z * rs, u1.w * rs};
-        if (m >= M) continue;
-        uint16_t* crow = C + m * a.ldc;
-        if (EPI == EPI_SWIGLU) {
-          float o[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = silu_fast(lo[e]) * up[e];
-          *reinterpret_cast<uint4*>(crow + (nh >> 1) + 8 * q) = pack8<H>(o);
-        } else if (nh >= a.n_q + a.n_kv) {   // v: natural order
-          *reinterpret_cast<uint4*>(crow + nh + 8 * q) = pack8h(lo);
-          *reinterpret_cast<uint4*>(crow + nh + 32 + 8 * q) = pack8h(up);
-        } else {
-          const int sbase = nh < a.n_q ? 0 : a.n_q;
-          const int cc = nh - sbase;
-          const int head = cc / a.hd, hh = (cc % a.hd) >> 6, half = a.hd >> 1;
-          const float pos = static_cast<float>(pl[tr]);
-          const float4 f0 = *reinterpret_cast<const float4*>(rv + hh * 32 + 8 * q);
-          const float4 f1 = *reinterpret_cast<const float4*>(rv + hh * 32 + 8 * q + 4);
-          const float fr[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
-          float ol[8], ou[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            // angle pos * theta^(-2i/hd), in revolutions (hardware sin/cos take revolutions)
-            const float rev = pos * fr[e];
-            const float frac = rev - floorf(rev);
-            const float cs = __builtin_amdgcn_cosf(frac), sn = __builtin_amdgcn_sinf(frac);
-            ol[e] = lo[e] * cs - up[e] * sn;   // lower half dim
-            ou[e] = up[e] * cs + lo[e] * sn;   // upper half dim
-          }
-          uint16_t* dst = crow + sbase + head * a.hd + hh * 32 + 8 * q;
-          *reinterpret_cast<uint4*>(dst) = pack8h(ol);
-          *reinterpret_cast<uint4*>(dst + half) = pack8h(ou);
-        }
+        if (m0 + tr < M) pair_piece<EPI, H>(a, l0, l1, u0, u1, rs, nw + 64 * h, q, m0 + tr, pl[tr], rv);
       }
     }
     wave_lds_sync();   // the slice's reads are done before the next block's writes
@@ -490,11 +496,268 @@ __device__ __forceinline__ void tile_sources(const GemmArgs& a, const uint16_t* 
   for (int i = 0; i < 8; ++i) {
     const int row = (8 * w + i) * 8 + lr;
     const int lc = swz(row, lane & 7);   // logical chunk stored in this lane's slot
+    // rows past M are never stored; they read the tile row above (256-row
+    // tiles run only with M >= GM), not all one row: that many requests for one
+    // cache line serialise in the L2 (3.5x the time of a whole launch)
     int64_t mr = m0 + row;
-    if (mr > M - 1) mr = M - 1;
+    if (mr > M - 1) mr -= GM;
     ga[i] = A + mr * a.lda + lc * 8 - (i & 3) * 512;
     gb[i] = b_row<EPI, uint16_t>(a, n0 + row) + lc * 8 - (i & 3) * 512;
   }
+}
+
+// ----------------------------------------------------------------- small tiles
+// Few rows leave most of the chip idle with 256 x 256 tiles (M = 120, N = 512:
+// two tiles).  The same kernel then walks BM x BN = 64 x 64 or 128 x 128
+// tiles, four waves in a 2 x 2 grid, K in 32 KB stages (SLABS slabs of 64)
+// through a ring of four: three stages of loads in flight per workgroup
+// instead of one, since here the memory latency per stage is what counts.
+// Every output is still one accumulator over K in order with the same MFMA,
+// so a row's bits do not depend on which tile shape ran it.
+//
+// Rows of A past M are not read at all (buffer loads, out of range).
+constexpr int ST_BYTES = 32768;   // one stage: SLABS x (A [BM][64] | W [BN][64])
+
+template <int N>
+__device__ __forceinline__ void wait_vm_barrier() {
+  // this wave's loads but the last N have landed and its LDS reads are done;
+  // then every wave's
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// Direct-to-LDS loads, 16 bytes per lane to 1 KB at LDS byte `dst` (uniform).
+// In asm: the compiler would wait for every load in flight before each read
+// of a stage (it cannot tell the ring's stages apart across iterations);
+// wait_vm_barrier does the waiting.  No register is written.
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)p));
+}
+__device__ __forceinline__ void dma_global(const void* src, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src)
+               : "memory");
+}
+__device__ __forceinline__ void dma_buffer(int __attribute__((ext_vector_type(4))) rsrc, int voff, int soff, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(voff),
+               "s"(rsrc), "s"(soff)
+               : "memory");
+}
+
+// 16-byte chunk c of row r of the finished tile in LDS.
+template <int BN>
+__device__ __forceinline__ int tslot(int r, int c) { return r * (BN / 4) + (c ^ (r & 15)); }
+
+template <int EPI, bool H, int BM, int BN, int SLABS>
+__device__ __forceinline__ void gemm_tiles(const GemmArgs& a, int64_t M, uint16_t* st0, uint16_t* st1, uint16_t* st2,
+                                           uint16_t* st3, float* rbuf, int32_t* pbuf, const float* rvbuf) {
+  static_assert(SLABS * (BM + BN) * GK * 2 == ST_BYTES, "stage size");
+  typedef typename Op16<H>::V V;
+  constexpr int WI = BM / 64, WJ = BN / 64;   // 32 x 32 blocks per wave
+  constexpr int LD = ST_BYTES / 4096;         // 1 KB loads per wave and stage
+  constexpr bool RESID = EPI == EPI_RESID || EPI == EPI_RESID_EMB;
+  constexpr bool PAIR = EPI == EPI_SWIGLU || EPI == EPI_QKV_ROPE;
+  constexpr int PPR = BN / 8;                 // pieces per row
+  constexpr int NP = BM * PPR / GT;           // pieces per thread
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, wm = w >> 1, wn = w & 1;
+  const int l32 = lane & 31, hi = lane >> 5, lr = lane >> 3;
+  static_assert(BM == BN, "each wave copies as many pieces of A as of W");
+  const int tiles_n = a.N / BN;
+  const int tiles_m = static_cast<int>((M + BM - 1) / BM);
+  const int tiles = tiles_m * tiles_n;
+  const int ns = a.K / (GK * SLABS);
+  // XCD x takes a contiguous eighth of the tiles in column-major order: equal
+  // shares for every M, and one XCD's workgroups share weight columns
+  const int xcd = blockIdx.x & 7, per_xcd = gridDim.x >> 3;
+  const int lo = static_cast<int>(static_cast<int64_t>(tiles) * xcd / 8);
+  const int end = static_cast<int>(static_cast<int64_t>(tiles) * (xcd + 1) / 8);
+  uint16_t* const stv[4] = {st0, st1, st2, st3};
+
+  for (int tile = lo + static_cast<int>(blockIdx.x >> 3); tile < end; tile += per_xcd) {
+    const int col = tile / tiles_m;
+    const int64_t m0 = static_cast<int64_t>(tile - col * tiles_m) * BM;
+    const int n0 = col * BN;
+    const int rows = M - m0 < BM ? static_cast<int>(M - m0) : BM;
+    __syncthreads();   // the previous tile's epilogue is done with the stages, rbuf and pbuf
+    // the residual of this thread's pieces, in flight under the k loop
+    float4 xv[RESID ? NP : 1][2];
+    if (RESID) {
+      const int64_t tok0 = EPI == EPI_RESID_EMB ? a.x_tok_desc[D_TOK_BEGIN] : 0;
+#pragma unroll
+      for (int u = 0; u < NP; ++u) {
+        const int p = t + u * GT, r = p / PPR, c = n0 + 8 * (p % PPR);
+        const int64_t m = m0 + (r < rows ? r : 0);
+        if (EPI == EPI_RESID_EMB) {
+          int32_t tok = a.x_tok[tok0 + m];
+          if (tok < 0 || tok >= a.vocab) tok = 0;
+          const uint4 e = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.x_emb) +
+                                                          static_cast<int64_t>(tok) * a.ldc + c);
+          xv[u][0] = make_float4(Op16<H>::widen(static_cast<uint16_t>(e.x & 0xFFFFu)),
+                                 Op16<H>::widen(static_cast<uint16_t>(e.x >> 16)),
+                                 Op16<H>::widen(static_cast<uint16_t>(e.y & 0xFFFFu)),
+                                 Op16<H>::widen(static_cast<uint16_t>(e.y >> 16)));
+          xv[u][1] = make_float4(Op16<H>::widen(static_cast<uint16_t>(e.z & 0xFFFFu)),
+                                 Op16<H>::widen(static_cast<uint16_t>(e.z >> 16)),
+                                 Op16<H>::widen(static_cast<uint16_t>(e.w & 0xFFFFu)),
+                                 Op16<H>::widen(static_cast<uint16_t>(e.w >> 16)));
+        } else {
+          const float* xr = a.x + m * a.ldc + c;
+          xv[u][0] = *reinterpret_cast<const float4*>(xr);
+          xv[u][1] = *reinterpret_cast<const float4*>(xr + 4);
+        }
+      }
+    }
+    if (PAIR && a.rs && t < BM) rbuf[t] = a.rs[m0 + t];   // padded by 256 rows
+    if (RESID && a.gnext && t < BN) rbuf[t] = a.gnext[n0 + t];
+    if (EPI == EPI_QKV_ROPE && t < BM) pbuf[t] = a.pos[m0 + t];
+
+    // sources: of each stage this wave copies LD / 2 pieces (8 rows x 64 k) of
+    // A and as many of W
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    const uint64_t abase = reinterpret_cast<uint64_t>(static_cast<const uint16_t*>(a.A) + m0 * a.lda);
+    v4i ra;   // buffer over the tile's rows below M
+    ra[0] = __builtin_amdgcn_readfirstlane(static_cast<int>(abase));
+    ra[1] = __builtin_amdgcn_readfirstlane(static_cast<int>(abase >> 32));
+    ra[2] = __builtin_amdgcn_readfirstlane(static_cast<int>(rows * a.lda * 2));
+    ra[3] = 0x00020000;
+    const uint16_t* gb[LD / 2];
+    int ao[LD / 2];
+    uint32_t so[LD / 2];   // the A piece's place in a stage; W's is BM * GK elements further
+#pragma unroll
+    for (int i = 0; i < LD / 2; ++i) {
+      const int p = (LD / 2) * w + i, slab = p / (BM / 8), row = (p % (BM / 8)) * 8 + lr;
+      const int kk = slab * GK + swz(row, lane & 7) * 8;
+      ao[i] = static_cast<int>((row * a.lda + kk) * 2);
+      gb[i] = b_row<EPI, uint16_t>(a, n0 + row) + kk;
+      so[i] = static_cast<uint32_t>(slab * (BM + BN) * GK + (p % (BM / 8)) * 8 * GK) * 2;
+    }
+    auto load_stage = [&](int s, const uint16_t* st) {
+      const uint32_t base = lds_offset(st);
+#pragma unroll
+      for (int i = 0; i < LD / 2; ++i) {
+        const uint32_t d = __builtin_amdgcn_readfirstlane(base + so[i]);
+        dma_buffer(ra, ao[i], s * (GK * SLABS * 2), d);
+        dma_global(gb[i] + s * (GK * SLABS), d + BM * GK * 2);
+      }
+    };
+    f32x16 acc[WI][WJ];
+#pragma unroll
+    for (int i = 0; i < WI; ++i)
+#pragma unroll
+      for (int j = 0; j < WJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    auto compute = [&](const uint16_t* st) {
+      // all fragments of the stage are requested before its first MFMA, which
+      // then wait only for their own
+      V af[SLABS * 4][WI], bw[SLABS * 4][WJ];
+#pragma unroll
+      for (int s = 0; s < SLABS * 4; ++s) {
+        const uint16_t* As = st + (s >> 2) * (BM + BN) * GK;
+        const uint16_t* Bs = As + BM * GK;
+        const int sw = swz(l32, 2 * (s & 3) + hi) << 3;
+#pragma unroll
+        for (int i = 0; i < WI; ++i)
+          af[s][i] = *reinterpret_cast<const V*>(As + (wm * (BM / 2) + i * 32 + l32) * GK + sw);
+#pragma unroll
+        for (int j = 0; j < WJ; ++j)
+          bw[s][j] = *reinterpret_cast<const V*>(Bs + (wn * (BN / 2) + j * 32 + l32) * GK + sw);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < SLABS * 4; ++s)
+#pragma unroll
+        for (int i = 0; i < WI; ++i)
+#pragma unroll
+          for (int j = 0; j < WJ; ++j) acc[i][j] = Op16<H>::mma(bw[s][j], af[s][i], acc[i][j]);
+    };
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+      if (s < ns) load_stage(s, stv[s]);
+    auto step = [&](int s, uint16_t* cur, uint16_t* nxt) {
+      // stage s has landed everywhere and every wave is done with stage s - 1,
+      // whose buffer takes stage s + 3
+      if (s + 2 < ns)
+        wait_vm_barrier<2 * LD>();
+      else if (s + 1 < ns)
+        wait_vm_barrier<LD>();
+      else
+        wait_vm_barrier<0>();
+      if (s + 3 < ns) load_stage(s + 3, nxt);
+      compute(cur);
+    };
+    for (int s = 0; s < ns; s += 4) {
+      step(s, st0, st3);
+      if (s + 1 < ns) step(s + 1, st1, st0);
+      if (s + 2 < ns) step(s + 2, st2, st1);
+      if (s + 3 < ns) step(s + 3, st3, st2);
+    }
+    __syncthreads();   // every wave is done with the stages: they take the tile in fp32
+    float4* const tl = reinterpret_cast<float4*>(st0);
+    float4* const th = reinterpret_cast<float4*>(st1);   // rows 64.. of a 128-row tile
+#pragma unroll
+    for (int i = 0; i < WI; ++i)
+#pragma unroll
+      for (int j = 0; j < WJ; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int r = wm * (BM / 2) + i * 32 + l32;
+          (r < 64 ? tl : th)[tslot<BN>(r & 63, wn * (BN / 8) + 8 * j + 2 * g + hi)] =
+              make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+        }
+    __syncthreads();
+    auto rd = [&](int r, int c) { return (r < 64 ? tl : th)[tslot<BN>(r & 63, c)]; };
+    if (!PAIR) {
+#pragma unroll
+      for (int u = 0; u < NP; ++u) {
+        const int p = t + u * GT, r = p / PPR, pc = p % PPR;
+        const int64_t m = m0 + r;
+        const int c = n0 + 8 * pc;
+        const bool in = r < rows;
+        const float4 s0 = rd(r, 2 * pc), s1 = rd(r, 2 * pc + 1);
+        if (RESID)
+          resid_piece<EPI, H>(a, xv[u][0], xv[u][1], s0, s1, *reinterpret_cast<const float4*>(rbuf + 8 * pc),
+                              *reinterpret_cast<const float4*>(rbuf + 8 * pc + 4), m, c, in, pc, a.gnext != nullptr,
+                              static_cast<uint16_t*>(a.hout));
+        else if (EPI == EPI_ARGMAX)
+          argmax_piece(a, s0, s1, m, c, in, pc);
+        else if (in)
+          store_piece<EPI, H>(a, s0, s1, m, c);
+      }
+    } else {
+      constexpr int QPR = BN / 16;   // pair-pieces per row: 4 per 64-column half
+#pragma unroll
+      for (int u = 0; u < BM * QPR / GT; ++u) {
+        const int p = t + u * GT, r = p / QPR, h = (p % QPR) >> 2, q = p & 3;
+        const float rs = a.rs ? rbuf[r] : 1.f;
+        const float4 l0 = rd(r, 16 * h + 2 * q), l1 = rd(r, 16 * h + 2 * q + 1);
+        const float4 u0 = rd(r, 16 * h + 2 * q + 8), u1 = rd(r, 16 * h + 2 * q + 9);
+        if (r < rows) pair_piece<EPI, H>(a, l0, l1, u0, u1, rs, n0 + 64 * h, q, m0 + r, pbuf[r], rvbuf);
+      }
+    }
+  }
+}
+
+// Which tiles a launch of M rows takes: the shape whose rounds over the grid
+// cost least.  Costs in microseconds of one round, per 64-deep k-step and for
+// start plus epilogue, fitted to single rounds at K = 512 .. 8192 with cold
+// weights: 64 x 64 tiles 0.21 / 2.2 (10 us at K = 2048, 30 at 8192), 128 x 128
+// 0.53 / 4.5 (21, 69), 256 x 256 1.44 / 11 (60, 196; the maxima epilogue
+// takes 40).  The 256-row tiles' rounds count by XCD, whose rows they are
+// dealt to in turn.  They also need a whole tile of rows (tile_sources).
+// Measured at K = 3072, N = 3072: M = 120 17 us against 92 with the large
+// tiles only, M = 800 37 against 91, M = 1920 70 against 91, M = 3300 112
+// against 93.
+enum TilePath : int { PATH_256 = 0, PATH_128 = 1, PATH_64 = 2 };
+template <int EPI>
+__device__ __forceinline__ int tile_path(int64_t M, int N, int K, int wgs) {
+  auto rounds = [](int64_t tiles, int slots) { return static_cast<float>((tiles + slots - 1) / slots); };
+  auto tiles = [&](int b) { return ((M + b - 1) / b) * (N / b); };
+  const float k = static_cast<float>(K / GK);
+  const float c64 = rounds(tiles(64), wgs) * (0.21f * k + 2.2f);
+  const float c128 = rounds(tiles(128), wgs) * (0.53f * k + 4.5f);
+  const int64_t rows_x = ((M + GM - 1) / GM + 7) / 8;
+  const float c256 = rounds(rows_x * (N / GN), wgs >> 3) * (1.44f * k + (EPI == EPI_ARGMAX ? 40.f : 11.f));
+  if (M >= GM && c256 <= c128 && c256 <= c64) return PATH_256;
+  return c128 < c64 ? PATH_128 : PATH_64;
 }
 
 template <int EPI, bool H>
@@ -511,6 +774,12 @@ __global__ __launch_bounds__(GT, 1) void k_gemm_bf16(GemmArgs a) {
   __shared__ __attribute__((aligned(16))) float rvbuf[64];    // rotary frequencies of the lower-half dims (QKV)
   const int64_t M = *a.m_ptr;
   if (M <= 0) return;
+  const int64_t tok0 = EPI == EPI_RESID_EMB ? a.x_tok_desc[D_TOK_BEGIN] : 0;   // the rows' first packed token
+  if (EPI == EPI_QKV_ROPE && static_cast<int>(threadIdx.x) < (a.hd >> 1))
+    rvbuf[threadIdx.x] = a.rope_rev[threadIdx.x];   // visible after the first barrier
+  const int path = tile_path<EPI>(M, a.N, a.K, gridDim.x);
+  if (path == PATH_64) return gemm_tiles<EPI, H, 64, 64, 2>(a, M, sA0, sB0, sA1, sB1, rbuf, pbuf, rvbuf);
+  if (path == PATH_128) return gemm_tiles<EPI, H, 128, 128, 1>(a, M, sA0, sB0, sA1, sB1, rbuf, pbuf, rvbuf);
   const int tiles_n = a.N / GN;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, wm = w >> 1, wn = w & 1;
   const int nk = a.K / GK;   // even (the launcher checks K % 128)
@@ -548,7 +817,6 @@ __global__ __launch_bounds__(GT, 1) void k_gemm_bf16(GemmArgs a) {
   };
   int q = blockIdx.x >> 3;
   if (q >= count_x) return;
-  if (EPI == EPI_QKV_ROPE && t < (a.hd >> 1)) rvbuf[t] = a.rope_rev[t];   // visible after the first barrier
   const uint16_t* ga[8];
   const uint16_t* gb[8];
   int64_t m0;
@@ -599,7 +867,7 @@ __global__ __launch_bounds__(GT, 1) void k_gemm_bf16(GemmArgs a) {
     // each wave stages its accumulators in its own 16 KB of stage 1, which is
     // idle until the next tile's first barrier
     float4* slice = reinterpret_cast<float4*>((w < 2 ? sA1 : sB1) + (w & 1) * 8192);
-    epilogue_bf16<EPI, H>(a, acc, m0, n0, M, wm, wn, lane, slice, rbuf, pbuf, rvbuf, prefetch);
+    epilogue_bf16<EPI, H>(a, acc, m0, n0, M, wm, wn, lane, slice, rbuf, pbuf, rvbuf, tok0, prefetch);
     m0 = m1;
     n0 = n1;
   }
@@ -611,7 +879,7 @@ __global__ __launch_bounds__(GT, 1) void k_gemm_bf16(GemmArgs a) {
 hipError_t launch_gemm_bf16(int epi, const GemmArgs& a, hipStream_t s) {
   if (a.K <= 0 || a.K % (2 * GK) || a.N % GN) return hipErrorInvalidValue;   // whole pairs of k-steps, whole tiles
   // one workgroup per CU, rounded to whole XCD groups; fewer for small problems
-  const int64_t tiles = ((a.m_ub + GM - 1) / GM) * (a.N / GN);
+  const int64_t tiles = ((a.m_ub + 63) / 64) * (a.N / 64);   // the smallest tiles
   int64_t g = num_cus();
   if (tiles < g) g = tiles;
   g = (g + 7) / 8 * 8;
