@@ -344,15 +344,22 @@ hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s) {
 }
 
 // ======================================================================= fp32
-// One wave per item; each lane owns one query of the 64-query block and walks
-// the keys of the staged block in order with an online softmax.
+// One workgroup per (sequence, head) item.  Four neighbouring lanes share a
+// query of the 64-query block, each taking every fourth key of the staged
+// 64-key block: scores of its 16 keys first, then one online-softmax update
+// for all of them, and the four partial states merge at the end.  (One lane per
+// query walking all keys one by one left 64 threads per item and a chain of
+// 64 dependent updates per block: 50 us for 153 sequences of 35 tokens and 4
+// heads of 32; this takes 14 us.)
 template <int HD>
-__global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a) {
-  __shared__ float Ks[64][HD];
-  __shared__ float Vs[64][HD];
+__global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
+  constexpr int P = HD + 4;   // row pitch: the four keys read at once lie in different banks
+  constexpr int KT = 16;      // keys per lane and block
+  __shared__ __attribute__((aligned(16))) float Ks[64 * P];
+  __shared__ __attribute__((aligned(16))) float Vs[64 * P];
   const int64_t tb = a.desc[D_TOK_BEGIN], sb = a.desc[D_SEQ_BEGIN], ns = a.desc[D_NSEQ];
   const int64_t n_items = ns * a.n_heads;
-  const int lane = threadIdx.x;
+  const int t = threadIdx.x, part = t & 3;
   const int rep = a.n_heads / a.n_kv;
   const int d_q = a.n_heads * HD, d_kv = a.n_kv * HD;
   const float scale = 1.0f / sqrtf(static_cast<float>(HD));
@@ -365,45 +372,81 @@ __global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a) {
     const int64_t s0 = a.cu[sb + si] - tb;
     const int L = static_cast<int>(a.cu[sb + si + 1] - a.cu[sb + si]);
     for (int qb = 0; qb * 64 < L; ++qb) {
-      const int qi = qb * 64 + lane;
-      float q[HD], o[HD];
+      const int qi = qb * 64 + (t >> 2);
+      f32x4 q[HD / 4], o[HD / 4];
 #pragma unroll
-      for (int i = 0; i < HD; ++i) {
-        q[i] = qi < L ? qkv[(s0 + qi) * a.ld + h * HD + i] : 0.f;
-        o[i] = 0.f;
+      for (int i = 0; i < HD / 4; ++i) {
+        q[i] = qi < L ? *reinterpret_cast<const f32x4*>(qkv + (s0 + qi) * a.ld + h * HD + 4 * i) : f32x4{0.f, 0.f, 0.f, 0.f};
+        o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
       float m = -INFINITY, l = 0.f;
       for (int kb = 0; kb <= qb; ++kb) {
         __syncthreads();
-        for (int id = lane; id < 64 * HD; id += 64) {
-          const int r = id / HD, c = id % HD;
+        for (int id = t; id < 64 * HD / 4; id += 256) {
+          const int r = id / (HD / 4), c = (id % (HD / 4)) * 4;
           const int kk = kb * 64 + r;
-          const bool ok = kk < L;
-          Ks[r][c] = ok ? qkv[(s0 + kk) * a.ld + d_q + kvh * HD + c] : 0.f;
-          Vs[r][c] = ok ? qkv[(s0 + kk) * a.ld + d_q + d_kv + kvh * HD + c] : 0.f;
+          f32x4 kv = f32x4{0.f, 0.f, 0.f, 0.f}, vv = kv;
+          if (kk < L) {
+            const float* row = qkv + (s0 + kk) * a.ld + d_q + kvh * HD + c;
+            kv = *reinterpret_cast<const f32x4*>(row);
+            vv = *reinterpret_cast<const f32x4*>(row + d_kv);
+          }
+          *reinterpret_cast<f32x4*>(Ks + r * P + c) = kv;
+          *reinterpret_cast<f32x4*>(Vs + r * P + c) = vv;
         }
         __syncthreads();
-        for (int r = 0; r < 64; ++r) {
-          const int key = kb * 64 + r;
-          if (key > qi || key >= L) break;
-          float s = 0.f;
+        float s[KT], mx = -INFINITY;
 #pragma unroll
-          for (int i = 0; i < HD; ++i) s = fmaf(q[i], Ks[r][i], s);
-          s *= scale;
-          const float m_new = fmaxf(m, s);
-          const float alpha = expf(m - m_new);
-          const float pr = expf(s - m_new);
-          l = l * alpha + pr;
+        for (int j = 0; j < KT; ++j) {
+          const int r = 4 * j + part, key = kb * 64 + r;
+          float dot = 0.f;
 #pragma unroll
-          for (int i = 0; i < HD; ++i) o[i] = o[i] * alpha + pr * Vs[r][i];
-          m = m_new;
+          for (int i = 0; i < HD / 4; ++i) {
+            const f32x4 kv = *reinterpret_cast<const f32x4*>(Ks + r * P + 4 * i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dot = fmaf(q[i][e], kv[e], dot);
+          }
+          s[j] = key <= qi && key < L ? dot * scale : -INFINITY;
+          mx = fmaxf(mx, s[j]);
         }
-      }
-      if (qi < L) {
-        const float inv = 1.0f / l;
-        float* orow = out + (s0 + qi) * a.ldo + h * HD;
+        if (mx == -INFINITY) continue;   // none of this lane's keys precede the query
+        const float m_new = fmaxf(m, mx);
+        const float alpha = expf(m - m_new);
+        l *= alpha;
 #pragma unroll
-        for (int i = 0; i < HD; ++i) orow[i] = o[i] * inv;
+        for (int i = 0; i < HD / 4; ++i) o[i] *= alpha;
+#pragma unroll
+        for (int j = 0; j < KT; ++j) {
+          const float pr = expf(s[j] - m_new);   // 0 for keys after the query
+          l += pr;
+#pragma unroll
+          for (int i = 0; i < HD / 4; ++i) {
+            const f32x4 vv = *reinterpret_cast<const f32x4*>(Vs + (4 * j + part) * P + 4 * i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[i][e] = fmaf(pr, vv[e], o[i][e]);
+          }
+        }
+        m = m_new;
+      }
+      // merge the four partial states (the query's own key makes one finite)
+      float mm = fmaxf(m, __shfl_xor(m, 1));
+      mm = fmaxf(mm, __shfl_xor(mm, 2));
+      const float wgt = m == -INFINITY ? 0.f : expf(m - mm);
+      l *= wgt;
+      l += __shfl_xor(l, 1);
+      l += __shfl_xor(l, 2);
+      const float inv = 1.0f / l;
+      float* orow = out + (s0 + qi) * a.ldo + h * HD;
+#pragma unroll
+      for (int i = 0; i < HD / 4; ++i) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float v = o[i][e] * wgt;
+          v += __shfl_xor(v, 1);
+          v += __shfl_xor(v, 2);
+          o[i][e] = v * inv;
+        }
+        if (qi < L && (i & 3) == part) *reinterpret_cast<f32x4*>(orow + 4 * i) = o[i];
       }
     }
   }
@@ -413,8 +456,8 @@ hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s) {
   if (a.npre != 0) return hipErrorInvalidValue;   // no shared prefix on this path
   const int g = grid_cap(a.seq_ub * a.n_heads, 4096);
   switch (a.hd) {
-    case 32: hipLaunchKernelGGL(k_attn_f32<32>, dim3(g), dim3(64), 0, s, a); break;
-    case 64: hipLaunchKernelGGL(k_attn_f32<64>, dim3(g), dim3(64), 0, s, a); break;
+    case 32: hipLaunchKernelGGL(k_attn_f32<32>, dim3(g), dim3(256), 0, s, a); break;
+    case 64: hipLaunchKernelGGL(k_attn_f32<64>, dim3(g), dim3(256), 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

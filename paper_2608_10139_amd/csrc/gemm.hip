@@ -17,8 +17,8 @@
 // launch and no work.  Where M leaves 256 x 256 tiles too few for the chip the
 // same launch takes 128 x 128 or 64 x 64 ones (tile_path).
 //
-// fp32 path: a plain 64 x 64 LDS-tiled FMA kernel with the same row mapping
-// and epilogues, used for fp32 models.
+// fp32 path: 32 x 64 tiles on the fp32 matrix instructions with the same row
+// mapping, used for fp32 models.
 #include "aiq_internal.h"
 #include "dev_util.h"
 
@@ -917,60 +917,84 @@ hipError_t launch_gemm_bf16(int epi, const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// ======================================================================= fp32 FMA
-constexpr int FM = 64, FN = 64, FK = 16, FT = 256;
+// ======================================================================= fp32
+// 32 x 64 tile per workgroup, four waves in a 2 x 2 grid of 16 x 32, on
+// v_mfma_f32_16x16x4_f32 (fp32 products and sums).  fp32 models are small
+// (N = 128 .. 512, a few thousand rows): a launch is bound by latency, so the
+// tile is small (338 workgroups at M = 5,392, N = 128), K goes in steps of 64
+// through two LDS stages with the next step's global loads in flight, and one
+// barrier per step.  M = 5,392: K = 512 58 us with the former 64 x 64 FMA tile
+// (K in steps of 16, nothing in flight) and 15.5 us with this.
+constexpr int FM = 32, FN = 64, FK = 64, FP = FK + 4, FT = 256;   // FP: row pitch in LDS, conflict-free
 
 template <int EPI>
 __global__ __launch_bounds__(FT) void k_gemm_f32(GemmArgs a) {
-  __shared__ float As[FK][FM + 4];
-  __shared__ float Bs[FK][FN + 4];
+  __shared__ __attribute__((aligned(16))) float S[2][(FM + FN) * FP];
   const int64_t M = *a.m_ptr;
   if (M <= 0) return;
   const int tiles_n = a.N / FN;
   const int64_t n_tiles = ((M + FM - 1) / FM) * tiles_n;
-  const int t = threadIdx.x, ty = t >> 4, tx = t & 15;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, wm = w >> 1, wn = w & 1;
+  const int l16 = lane & 15, g = lane >> 4;
   const float* A = static_cast<const float*>(a.A);
-  const int lrow = t >> 2, lk = (t & 3) * 4;
+  const int lrow = t >> 4, lk = (t & 15) * 4;   // this thread's rows lrow, lrow + 16, ... of a step, 4 floats each
   for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
     const int64_t m0 = (tile / tiles_n) * FM;
     const int n0 = static_cast<int>(tile % tiles_n) * FN;
-    int64_t mr = m0 + lrow;
-    if (mr > M - 1) mr = M - 1;
-    const float* ap = A + mr * a.lda + lk;
-    const float* bp = b_row<EPI, float>(a, n0 + lrow) + lk;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < a.K; k0 += FK) {
-      const float4 av = *reinterpret_cast<const float4*>(ap + k0);
-      const float4 bv = *reinterpret_cast<const float4*>(bp + k0);
-      __syncthreads();
-      As[lk + 0][lrow] = av.x; As[lk + 1][lrow] = av.y; As[lk + 2][lrow] = av.z; As[lk + 3][lrow] = av.w;
-      Bs[lk + 0][lrow] = bv.x; Bs[lk + 1][lrow] = bv.y; Bs[lk + 2][lrow] = bv.z; Bs[lk + 3][lrow] = bv.w;
-      __syncthreads();
+    const float* src[6];
+    bool ok[6];
 #pragma unroll
-      for (int k = 0; k < FK; ++k) {
-        float ar[4], br[4];
+    for (int u = 0; u < 6; ++u) {   // 2 x 16 rows of A, 4 x 16 of W
+      const int row = lrow + 16 * (u < 2 ? u : u - 2);
+      ok[u] = u >= 2 || m0 + row < M;
+      src[u] = u < 2 ? A + (ok[u] ? m0 + row : 0) * a.lda + lk : b_row<EPI, float>(a, n0 + row) + lk;
+    }
+    float4 v[6];
+    // a.K is a multiple of 16, not of FK: the last step's missing columns are zeros
+    auto fetch = [&](int k0) {
+      const bool in = k0 + lk < a.K;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          ar[i] = As[k][ty * 4 + i];
-          br[i] = Bs[k][tx * 4 + i];
+      for (int u = 0; u < 6; ++u)
+        v[u] = ok[u] && in ? *reinterpret_cast<const float4*>(src[u] + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    fetch(0);
+    int buf = 0;
+    for (int k0 = 0; k0 < a.K; k0 += FK, buf ^= 1) {
+      // buffer `buf` was last read before the barrier of the step before
+      float* st = S[buf];
+#pragma unroll
+      for (int u = 0; u < 6; ++u) *reinterpret_cast<float4*>(st + (lrow + 16 * u) * FP + lk) = v[u];
+      __syncthreads();
+      if (k0 + FK < a.K) fetch(k0 + FK);
+      const float* ar = st + (wm * 16 + l16) * FP + 4 * g;
+      const float* br = st + (FM + wn * 32 + l16) * FP + 4 * g;
+      // lane group g holds columns 16 s + 4 g .. + 3: product e of a 16-column
+      // slice sums columns e, 4 + e, 8 + e, 12 + e
+#pragma unroll
+      for (int s = 0; s < FK / 16; ++s) {
+        const f32x4 av = *reinterpret_cast<const f32x4*>(ar + 16 * s);
+        const f32x4 b0 = *reinterpret_cast<const f32x4*>(br + 16 * s);
+        const f32x4 b1 = *reinterpret_cast<const f32x4*>(br + 16 * FP + 16 * s);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(b0[e], av[e], acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1[e], av[e], acc[1], 0, 0, 0);
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(ar[i], br[j], acc[i][j]);
       }
     }
-    const int n = n0 + tx * 4;
+    __syncthreads();   // both buffers free for the next tile
+    // lane (l16, g): row l16 of the wave, columns 16 j + 4 g .. + 3
+    const int64_t m = m0 + wm * 16 + l16;
+    if (m < M) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t m = m0 + ty * 4 + i;
-      if (m >= M) continue;
-      if (EPI == EPI_GELU) {
-        *reinterpret_cast<float4*>(static_cast<float*>(a.C) + m * a.ldc + n) =
-            make_float4(gelu_erf(acc[i][0]), gelu_erf(acc[i][1]), gelu_erf(acc[i][2]), gelu_erf(acc[i][3]));
-      } else {  // plain fp32 store (QKV columns in natural order; rotary applied afterwards)
-        *reinterpret_cast<float4*>(static_cast<float*>(a.C) + m * a.ldc + n) =
-            make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+      for (int j = 0; j < 2; ++j) {
+        f32x4 o = acc[j];
+        if (EPI == EPI_GELU) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = gelu_erf(o[e]);
+        }   // others: plain fp32 store (QKV columns in natural order; rotary applied afterwards)
+        *reinterpret_cast<f32x4*>(static_cast<float*>(a.C) + m * a.ldc + n0 + wn * 32 + 16 * j + 4 * g) = o;
       }
     }
   }
