@@ -950,12 +950,10 @@ __global__ __launch_bounds__(FT) void k_gemm_f32(GemmArgs a) {
       src[u] = u < 2 ? A + (ok[u] ? m0 + row : 0) * a.lda + lk : b_row<EPI, float>(a, n0 + row) + lk;
     }
     float4 v[6];
-    // a.K is a multiple of 16, not of FK: the last step's missing columns are zeros
     auto fetch = [&](int k0) {
-      const bool in = k0 + lk < a.K;
 #pragma unroll
       for (int u = 0; u < 6; ++u)
-        v[u] = ok[u] && in ? *reinterpret_cast<const float4*>(src[u] + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
+        v[u] = ok[u] ? *reinterpret_cast<const float4*>(src[u] + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
     };
     f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
     fetch(0);
@@ -1001,6 +999,7 @@ __global__ __launch_bounds__(FT) void k_gemm_f32(GemmArgs a) {
 }
 
 hipError_t launch_gemm_f32(int epi, const GemmArgs& a, hipStream_t s) {
+  if (a.K <= 0 || a.K % FK || a.N % FN) return hipErrorInvalidValue;   // whole k-steps, whole tiles
   const int64_t tiles = ((a.m_ub + FM - 1) / FM) * (a.N / FN);
   int64_t g = static_cast<int64_t>(num_cus()) * 4;
   if (tiles < g) g = tiles;

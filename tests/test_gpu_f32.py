@@ -1,0 +1,40 @@
+"""The fp32 path (32 x 64 projection tiles, attention with four lanes per query)
+at the edges of its tiles and key blocks, for head dims 32 and 64, MHA and
+GQA, against the fp64 oracle at the fp32 tolerance; a sequence's bits do not
+depend on the others in its batch."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2608_10139_amd.device import DeviceModel, DevicePrefill
+from synth.configs import ModelSpec
+from synth.gen import make_model
+from tests._parity import TOL_F32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,heads,kv,ff", [(128, 4, 2, 64), (64, 2, 2, 192), (256, 4, 1, 512)])
+def test_f32_model(d, heads, kv, ff):
+    spec = ModelSpec(n_layers=2, d_model=d, n_heads=heads, n_kv_heads=kv, d_ff=ff, vocab=256, act="gelu", dtype="f32",
+                     weight_seed=61, init_std=0.05)
+    if (spec.d_q + 2 * spec.d_kv) % 64:
+        pytest.skip("not a supported width")
+    m = make_model(spec)
+    dm = DeviceModel(m)
+    r = np.random.default_rng(3)
+    seqs = [r.integers(0, 256, n).astype(np.int32) for n in (1, 2, 3, 4, 5, 31, 32, 33, 63, 64, 65, 127, 128, 129, 200)]
+
+    def run(batch):
+        cu = np.zeros(len(batch) + 1, dtype=np.int32)
+        cu[1:] = np.cumsum([len(s) for s in batch])
+        pf = DevicePrefill(None, max_tokens=int(cu[-1]), dmodel=dm)
+        out = pf.run(torch.from_numpy(np.concatenate(batch)).cuda(), torch.from_numpy(cu).cuda()).cpu().numpy()
+        pf.close()
+        return out
+
+    got = run(seqs)
+    assert np.abs(got - oracle.label_logits(m, seqs, (1, 2))).max() <= TOL_F32
+    for i, s in enumerate(seqs):
+        assert np.array_equal(run([s])[0], got[i]), len(s)
