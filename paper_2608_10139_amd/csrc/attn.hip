@@ -1,8 +1,8 @@
 // Causal self-attention over the packed variable-length batch, grouped K/V
 // heads (query head j reads K/V head j / (n_heads / n_kv)).
 //
-// Work items are (sequence, K/V head, head group) walked by a persistent
-// grid; a workgroup holds REP of the n_heads / n_kv query heads that read one
+// Work items are (sequence, K/V head, head group), split by query block where
+// they are few, walked by a persistent grid; a workgroup holds REP of the n_heads / n_kv query heads that read one
 // K/V head (all of them when registers allow), four waves per query head, so
 // each staged key block serves all of them (its global reads happen once per
 // group instead of once per query head).  An item loops over 64-query blocks of its own sequence and, inside,
@@ -52,6 +52,8 @@ static int grid_cap(int64_t items, int cap) {
 
 
 // ======================================================================= bf16 MFMA
+constexpr int MAX_SPLIT = 16;   // most shares of an item's query blocks
+
 template <int HD, int REP>
 __global__ __launch_bounds__(256 * REP) void k_attn_bf16(AttnArgs a) {
   constexpr int KB = 64;            // keys per block
@@ -68,6 +70,13 @@ __global__ __launch_bounds__(256 * REP) void k_attn_bf16(AttnArgs a) {
   const int64_t tb = a.desc[D_TOK_BEGIN], sb = a.desc[D_SEQ_BEGIN], ns = a.desc[D_NSEQ];
   const int groups = a.n_heads / (a.n_kv * REP);   // head groups per K/V head
   const int64_t n_items = ns * a.n_kv * groups;
+  // Few items (a small batch) leave workgroups without one while a long
+  // sequence's query blocks run one after another (8 sequences of up to 560
+  // tokens, 64 items: 149 us, 51 us split): a unit is then one of `split`
+  // interleaved shares of an item's query blocks.  Query blocks are
+  // independent, so the results are the same bits.
+  const int split = n_items * 2 > gridDim.x ? 1 : static_cast<int>(n_items * MAX_SPLIT > gridDim.x ? gridDim.x / n_items : MAX_SPLIT);
+  const int64_t n_units = n_items * split;
   const int t = threadIdx.x, lane = t & 63, g = lane >> 4, c16 = lane & 15;
   const int w = (t >> 6) & 3;      // the wave's 16 queries of a 64-query block
   const int hq = t >> 8;           // its query head inside the workgroup's group
@@ -83,21 +92,22 @@ __global__ __launch_bounds__(256 * REP) void k_attn_bf16(AttnArgs a) {
   // key block and the queries of the next task are read while the last key
   // block of the current one is consumed.
   struct Task {
-    int64_t item, s0;   // item, first packed row of the sequence's own rows
+    int64_t unit, s0;   // unit, first packed row of the sequence's own rows
     int L, qb, h0;       // positions (prefix + own), query block, first query head of the group
   };
-  // first task of the first item at or after `item` that has own rows
-  auto item_task = [&](int64_t item, Task& tk) -> bool {
-    for (; item < n_items; item += gridDim.x) {
+  // first task of the first unit at or after `unit` that has one
+  auto unit_task = [&](int64_t unit, Task& tk) -> bool {
+    for (; unit < n_units; unit += gridDim.x) {
       const int per_seq = a.n_kv * groups;
-      const int64_t si = static_cast<int32_t>(item) / per_seq;   // items < 2^31 (checked at launch)
+      const int32_t item = static_cast<int32_t>(unit) / split;   // units < 2^31 (checked at launch)
+      const int64_t si = item / per_seq;
       const int64_t c0 = a.cu[sb + si], c1 = a.cu[sb + si + 1];
-      if (c1 > c0) {
+      tk.L = static_cast<int>(c1 - c0) + np;
+      tk.qb = np / KB + (static_cast<int32_t>(unit) - item * split);
+      if (c1 > c0 && tk.qb * KB < tk.L) {
         const int r = static_cast<int>(item - si * per_seq);   // K/V head r / groups, group r % groups
-        tk.item = item;
+        tk.unit = unit;
         tk.s0 = c0 - tb;
-        tk.L = static_cast<int>(c1 - c0) + np;
-        tk.qb = np / KB;
         tk.h0 = r * REP;   // K/V head r / groups owns query heads (r / groups) * rep ..
         return true;
       }
@@ -105,12 +115,12 @@ __global__ __launch_bounds__(256 * REP) void k_attn_bf16(AttnArgs a) {
     return false;
   };
   auto advance = [&](const Task& c, Task& n) -> bool {
-    if ((c.qb + 1) * KB < c.L) {
+    if ((c.qb + split) * KB < c.L) {
       n = c;
-      n.qb = c.qb + 1;
+      n.qb = c.qb + split;
       return true;
     }
-    return item_task(c.item + gridDim.x, n);
+    return unit_task(c.unit + gridDim.x, n);
   };
   // row of position p: the prefix's rows, then the sequence's own rows
   auto row_of = [&](const Task& tk, int p) {
@@ -149,7 +159,7 @@ __global__ __launch_bounds__(256 * REP) void k_attn_bf16(AttnArgs a) {
   };
 
   Task cur;
-  if (!item_task(blockIdx.x, cur)) return;
+  if (!unit_task(blockIdx.x, cur)) return;
   half8 qf[HD / 32];
   load_q(cur, qf);
   fetch(cur, 0);
@@ -321,7 +331,7 @@ hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s) {
   // about 32 query heads' worth of workgroups per CU: with work items of very
   // unequal length (sequence lengths spread 16..512) a fine grid balances the
   // tail better
-  const int g = grid_cap(items, 8192 / hpw);
+  const int g = grid_cap(items * MAX_SPLIT, 8192 / hpw);
 #define AIQ_ATTN(HD, R) hipLaunchKernelGGL((k_attn_bf16<HD, R>), dim3(g), dim3(256 * R), 0, s, a)
   if (a.hd == 64) {
     switch (hpw) {

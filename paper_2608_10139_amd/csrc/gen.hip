@@ -28,11 +28,6 @@ __device__ __forceinline__ float wave_sum_g(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;
 }
-__device__ __forceinline__ float wave_max_g(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
-}
 
 // ------------------------------------------------------------------ descriptors
 __global__ void k_gen_desc(const int64_t* cd, int64_t* gd, int64_t* cnt, int32_t nb) {
@@ -183,26 +178,54 @@ hipError_t launch_gen_embed(const int64_t* gen_desc, const int64_t* cu, const in
 }
 
 // ------------------------------------------------------------------ decode attention
-// Wave per (sequence, K/V head): the REP = n_heads / n_kv query heads of the
-// group against every kept key of the sequence (prompt, earlier generated
+// Workgroup per (sequence, K/V head): the REP = n_heads / n_kv query heads of
+// the group against every kept key of the sequence (prompt, earlier generated
 // tokens, this token).  A key row of HD fp16 values is read by LPK = HD / 8
 // lanes, 16 bytes each, so one wave load covers 64 / LPK whole rows; keys go
-// in blocks of 4 such loads (an online-softmax step), the next block's key
-// and value rows in flight while the current one is used.  Each lane keeps
-// its 8 query dims and 8 output dims per head; partial dot products meet
-// over the LPK lanes of a row, partial outputs over the key groups at the
-// end.  The wave also stores this step's key and value into the generated
-// cache.
+// in blocks of 4 such loads, block b to wave b mod 4, a wave's next block in
+// flight while the current one is used.  Every lane group keeps its own
+// running maximum and sum over the keys it reads, so a block needs no exchange
+// between lanes but its dot products over the LPK lanes of a row (DPP moves);
+// groups, then waves, merge at the end.  Bound: HBM for many sequences (each
+// kept key and value row once), the chain of blocks for few.  One wave per
+// item with the maximum and the sum of every block reduced over the wave
+// through the LDS crossbar took 32 us per step for 256 sequences of 170 keys
+// (8 heads of 64) and 98 us for 8 sequences of up to 560 (groups of 3, heads of
+// 128); this takes 25 and 20 us (but 7 % more than
+// before for 3,276 sequences and groups of 1, at 4 TB/s).  The split depends on the keys alone, so a
+// sequence's bits do not depend on the batch.  The workgroup also stores this step's key
+// and value into the generated cache.
+__device__ __forceinline__ float dpp_add(float v, int lanes) {
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));    // lane ^ 1
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));    // lane ^ 2
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, false));   // the other quad of 8
+  if (lanes == 16)
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, false));   // the other 8 of 16
+  return v;
+}
+
+// v combined over the wave's lane groups of LPK (8 or 16) lanes, in every lane:
+// the halves of 16-lane rows (row_ror:8), then v_permlane16_swap (rows paired)
+// and v_permlane32_swap (halves of the wave); no LDS.
+template <int LPK, typename F>
+__device__ __forceinline__ float across_groups(float v, F f) {
+  if (LPK == 8) v = f(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xF, 0xF, false)));
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 template <int HD, int REP>
 __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
   constexpr int LPK = HD / 8;     // lanes per key row
   constexpr int KPI = 64 / LPK;   // key rows per wave load
   constexpr int IT = 4;           // wave loads per block
-  constexpr int KB = KPI * IT;    // keys per online-softmax block
+  constexpr int KB = KPI * IT;    // keys per block
+  constexpr int NW = 4;           // waves per item
+  __shared__ float so[NW][REP][HD], sm[NW][REP], sl[NW][REP];
   const int64_t n = a.gen_desc[D_NSEQ], sb = a.gen_desc[D_SEQ_BEGIN], tb = a.chunk_desc[D_TOK_BEGIN];
-  const int lane = threadIdx.x & 63, gk = lane / LPK, c = lane % LPK;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, gk = lane / LPK, c = lane % LPK;
   const int d_q = a.n_heads * HD, d_kv = a.n_kv * HD;
   const float scale = 1.4426950408889634f / sqrtf(static_cast<float>(HD));   // log2(e) / sqrt(hd)
   const uint16_t* qkv = static_cast<const uint16_t*>(a.qkv);
@@ -213,20 +236,20 @@ __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
   const int64_t ld = a.ld;
   const int64_t items = n * a.n_kv;
 
-  for (int64_t item = wave; item < items; item += n_waves) {
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
     const int64_t i = item / a.n_kv;
     const int kvh = static_cast<int>(item % a.n_kv);
     const int64_t s0 = a.cu[sb + i] - tb;
     const int own = static_cast<int>(a.cu[sb + i + 1] - a.cu[sb + i]);
     const int P = a.npre + own;   // prompt positions
-    if (a.last_row && own == 0) continue;   // no own row to attend from (same for the whole wave)
+    if (a.last_row && own == 0) continue;   // no own row to attend from (same for the whole workgroup)
     // keys: the prompt, the earlier generated tokens, this token (last-row
     // mode: the prompt, whose last row is the query)
     const int N = a.last_row ? P : P + a.step + 1;
     const uint16_t* qrow = !a.last_row ? qkv + i * ld : (qkv ? qkv + i * a.ldq : kvc + (s0 + own - 1) * ld);
     const int kc = d_q + kvh * HD, vc = d_q + d_kv + kvh * HD;   // key / value columns of a q|k|v row
     uint16_t* gslot = a.last_row ? nullptr : gkv + (i * a.gen + a.step) * (2 * d_kv);
-    if (!a.last_row && lane < 2 * LPK) {
+    if (!a.last_row && w == 0 && lane < 2 * LPK) {
       const bool isv = lane >= LPK;
       const int cc = lane % LPK;
       *reinterpret_cast<uint4*>(gslot + (isv ? d_kv : 0) + kvh * HD + cc * 8) =
@@ -285,10 +308,10 @@ __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
       for (int e = 0; e < 8; ++e) o[r][e] = 0.f;
     }
     uint4 kr[IT], vr[IT];
-    load_block(0, kr, vr);
-    for (int kb = 0; kb < N; kb += KB) {
+    if (w * KB < N) load_block(w * KB, kr, vr);
+    for (int kb = w * KB; kb < N; kb += NW * KB) {
       uint4 kn[IT], vn[IT];
-      if (kb + KB < N) load_block(kb + KB, kn, vn);   // next block in flight
+      if (kb + NW * KB < N) load_block(kb + NW * KB, kn, vn);   // next block in flight
       float s[REP][IT];
 #pragma unroll
       for (int it = 0; it < IT; ++it) {
@@ -305,8 +328,7 @@ __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
           float dot = 0.f;
 #pragma unroll
           for (int e = 0; e < 8; ++e) dot = fmaf(qf[r][e], kf[e], dot);
-#pragma unroll
-          for (int off = 1; off < LPK; off <<= 1) dot += __shfl_xor(dot, off);
+          dot = dpp_add(dot, LPK);
           s[r][it] = ok ? dot : -INFINITY;
         }
       }
@@ -322,19 +344,18 @@ __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
       }
 #pragma unroll
       for (int r = 0; r < REP; ++r) {
-        float mx = s[r][0];
+        float mx = m[r];
 #pragma unroll
-        for (int it = 1; it < IT; ++it) mx = fmaxf(mx, s[r][it]);
-        const float m_new = fmaxf(m[r], wave_max_g(mx));   // finite: key kb is valid
-        const float alpha = exp2f(m[r] - m_new);
+        for (int it = 0; it < IT; ++it) mx = fmaxf(mx, s[r][it]);
+        const float ref = mx == -INFINITY ? 0.f : mx;   // no key of this group yet: every term below is 0
+        const float alpha = __builtin_amdgcn_exp2f(m[r] - ref);
         float p[IT], ps = 0.f;
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-          p[it] = exp2f(s[r][it] - m_new);   // 0 for keys past the end (score -inf)
+          p[it] = __builtin_amdgcn_exp2f(s[r][it] - ref);   // 0 for keys past the end (score -inf)
           ps += p[it];
         }
-        // every key's probability sits in its LPK lanes: count it once
-        l[r] = l[r] * alpha + wave_sum_g(c == 0 ? ps : 0.f);
+        l[r] = l[r] * alpha + ps;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           float acc = o[r][e] * alpha;
@@ -342,9 +363,9 @@ __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
           for (int it = 0; it < IT; ++it) acc = fmaf(p[it], vf[it][e], acc);
           o[r][e] = acc;
         }
-        m[r] = m_new;
+        m[r] = mx;
       }
-      if (kb + KB < N) {
+      if (kb + NW * KB < N) {
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
           kr[it] = kn[it];
@@ -352,23 +373,44 @@ __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
         }
       }
     }
-    // partial outputs of the key groups (lanes with the same dims) add up
+    // the key groups of the wave, then the waves (key 0 makes one maximum finite)
+    auto add = [](float x, float y) { return x + y; };
+    auto max2 = [](float x, float y) { return fmaxf(x, y); };
 #pragma unroll
     for (int r = 0; r < REP; ++r) {
+      const float mw = across_groups<LPK>(m[r], max2);
+      const float f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[r] - mw);
+      const float lw = across_groups<LPK>(l[r] * f, add);
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-#pragma unroll
-        for (int off = LPK; off < 64; off <<= 1) o[r][e] += __shfl_xor(o[r][e], off);
+      for (int e = 0; e < 8; ++e) o[r][e] = across_groups<LPK>(o[r][e] * f, add);
       if (gk == 0) {
-        const float inv = 1.0f / l[r];
-        uint32_t pk[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          pk[e] = f2act(o[r][2 * e] * inv, a.out_act) |
-                  (static_cast<uint32_t>(f2act(o[r][2 * e + 1] * inv, a.out_act)) << 16);
-        *reinterpret_cast<uint4*>(out + i * d_q + (kvh * REP + r) * HD + c * 8) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+        for (int e = 0; e < 8; ++e) so[w][r][c * 8 + e] = o[r][e];
+        if (c == 0) {
+          sm[w][r] = mw;
+          sl[w][r] = lw;
+        }
       }
     }
+    __syncthreads();
+    for (int j = threadIdx.x; j < REP * HD / 2; j += 256) {   // two output values per thread
+      const int r = j / (HD / 2), e = (j % (HD / 2)) * 2;
+      float mm = sm[0][r];
+#pragma unroll
+      for (int v = 1; v < NW; ++v) mm = fmaxf(mm, sm[v][r]);
+      float ls = 0.f, o0 = 0.f, o1 = 0.f;
+#pragma unroll
+      for (int v = 0; v < NW; ++v) {
+        const float f = __builtin_amdgcn_exp2f(sm[v][r] - mm);   // 0 for a wave without keys
+        ls = fmaf(sl[v][r], f, ls);
+        o0 = fmaf(so[v][r][e], f, o0);
+        o1 = fmaf(so[v][r][e + 1], f, o1);
+      }
+      const float inv = 1.0f / ls;
+      *reinterpret_cast<uint32_t*>(out + i * d_q + (kvh * REP + r) * HD + e) =
+          f2act(o0 * inv, a.out_act) | (static_cast<uint32_t>(f2act(o1 * inv, a.out_act)) << 16);
+    }
+    __syncthreads();   // the partial states are read before the next item writes them
   }
 }
 
@@ -377,7 +419,7 @@ hipError_t launch_attention_gen(const GenAttnArgs& a, hipStream_t s) {
       (!a.last_row && (a.step < 0 || a.step >= a.gen || !a.gkv || !a.qkv)))
     return hipErrorInvalidValue;
   const int rep = a.n_heads / a.n_kv;
-  const dim3 grid(grid_for(a.seq_ub * a.n_kv, 4, 8192)), block(256);
+  const dim3 grid(grid_for(a.seq_ub * a.n_kv, 1, 16384)), block(256);
 #define AIQ_GEN_ATTN(HD_)                                                          \
   switch (rep) {                                                                   \
     case 1: hipLaunchKernelGGL((k_attn_gen<HD_, 1>), grid, block, 0, s, a); break; \
