@@ -182,8 +182,8 @@ hipError_t launch_gen_embed(const int64_t* gen_desc, const int64_t* cu, const in
 // the group against every kept key of the sequence (prompt, earlier generated
 // tokens, this token).  A key row of HD fp16 values is read by LPK = HD / 8
 // lanes, 16 bytes each, so one wave load covers 64 / LPK whole rows; keys go
-// in blocks of 4 such loads, block b to wave b mod 4, a wave's next block in
-// flight while the current one is used.  Every lane group keeps its own
+// in blocks of 4 such loads, block b to wave b mod 4 (no second block in flight:
+// its registers cost more in waves per SIMD, 3 for 5, than it hides).  Every lane group keeps its own
 // running maximum and sum over the keys it reads, so a block needs no exchange
 // between lanes but its dot products over the LPK lanes of a row (DPP moves);
 // groups, then waves, merge at the end.  Bound: HBM for many sequences (each
@@ -191,10 +191,10 @@ hipError_t launch_gen_embed(const int64_t* gen_desc, const int64_t* cu, const in
 // item with the maximum and the sum of every block reduced over the wave
 // through the LDS crossbar took 32 us per step for 256 sequences of 170 keys
 // (8 heads of 64) and 98 us for 8 sequences of up to 560 (groups of 3, heads of
-// 128); this takes 25 and 20 us (but 7 % more than
-// before for 3,276 sequences and groups of 1, at 4 TB/s).  The split depends on the keys alone, so a
-// sequence's bits do not depend on the batch.  The workgroup also stores this step's key
-// and value into the generated cache.
+// 128); this takes 23 and 21 us (and 231 us against 228 for 3,276 sequences and groups
+// of 1, at 4.1 TB/s).  The split depends on the keys alone, so a sequence's
+// bits do not depend on the batch.  The workgroup also stores this step's key and
+// value into the generated cache.
 __device__ __forceinline__ float dpp_add(float v, int lanes) {
   v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));    // lane ^ 1
   v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));    // lane ^ 2
@@ -307,11 +307,9 @@ __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) o[r][e] = 0.f;
     }
-    uint4 kr[IT], vr[IT];
-    if (w * KB < N) load_block(w * KB, kr, vr);
     for (int kb = w * KB; kb < N; kb += NW * KB) {
-      uint4 kn[IT], vn[IT];
-      if (kb + NW * KB < N) load_block(kb + NW * KB, kn, vn);   // next block in flight
+      uint4 kr[IT], vr[IT];
+      load_block(kb, kr, vr);
       float s[REP][IT];
 #pragma unroll
       for (int it = 0; it < IT; ++it) {
@@ -364,13 +362,6 @@ __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
           o[r][e] = acc;
         }
         m[r] = mx;
-      }
-      if (kb + NW * KB < N) {
-#pragma unroll
-        for (int it = 0; it < IT; ++it) {
-          kr[it] = kn[it];
-          vr[it] = vn[it];
-        }
       }
     }
     // the key groups of the wave, then the waves (key 0 makes one maximum finite)
