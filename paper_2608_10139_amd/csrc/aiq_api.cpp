@@ -159,7 +159,7 @@ aiq_status validate_model(const aiq_model* m) {
 struct Layout {
   size_t ctr, mask, blk_cnt, blk_off, sel, payload, lens, label, logits, cu, blk_tok, tok_off, packed, hkeys, hvals,
       bins, desc, rcos, rsin, rrev, x, delta, h, qkv, att, ffn, pos, hf, ssp, rs, pkv, ptok, pcu, pdesc, pxlast,
-      kvc, gkv, glog, gtok, gdone, gen, gdesc, gcnt, kcount, koff, prank, psorted, pcnt, poff, pscan, pa, pb,
+      kvc, gkv, glog, gdone, gen, gdesc, gcnt, kcount, koff, prank, psorted, pcnt, poff, pscan, pa, pb,
       lb, xl, ldesc, laux, jkeys, jvals, jlog2, gslot, gkey0, gval0, gkey1, gval1, ghist, gn, total;
 };
 
@@ -292,7 +292,6 @@ Layout run_layout(const aiq_plan* p) {
     L.gkv = c.take(static_cast<size_t>(p->n_layers) * su * G * 2 * p->d_kv * ab);
     L.hf = c.take(su * d * ab);
     L.glog = c.take(std::min<size_t>(su, GEN_HEAD_ROWS) * (p->model.vocab / 64) * 8);   // per-64-column maxima
-    L.gtok = c.take(su * 4);
     L.gdone = c.take(su * 4);
     L.gen = c.take(static_cast<size_t>(n + 1) * G * 4);
     L.gdesc = c.take(D_STRIDE * 8);
@@ -402,7 +401,7 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
   const float eps = static_cast<float>(m.norm_eps);
   auto gemm = [&](int epi, const void* A, int64_t lda, int N, int K, const void* B0, const void* B1, const void* B2,
                   void* C, int64_t ldc, const float* gnext = nullptr, const int64_t* rows_ptr = nullptr,
-                  int64_t rows_ub = 0, float* xr = nullptr, bool x_table = false) {
+                  int64_t rows_ub = 0, float* xr = nullptr, bool x_table = false, bool from_ssp = false) {
     GemmArgs g{};
     g.A = A;
     g.lda = lda;
@@ -424,6 +423,8 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
     g.rope_rev = rrev;
     g.f16 = p->act == 2;
     g.rs = rs;
+    g.ssp_in = from_ssp ? ssp : nullptr;
+    g.eps = eps;
     if (epi == EPI_RESID) {
       g.x = xr ? xr : x;
       g.gnext = gnext;
@@ -444,7 +445,7 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
   // and n_kv key columns, then values, with its own rows, row scales and positions
   auto gemm_part = [&](const void* A, const int64_t* rows_ptr, int64_t rows_ub, int N, int n_q, int n_kv,
                        const void* B0, const void* B1, const void* B2, void* C, int64_t ldc, const float* rsr,
-                       const int32_t* posr) {
+                       const int32_t* posr, bool from_ssp) {
     GemmArgs g{};
     g.A = A;
     g.lda = d;
@@ -464,6 +465,8 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
     g.rope_rev = rrev;
     g.f16 = p->act == 2;
     g.rs = rsr;
+    g.ssp_in = from_ssp ? ssp : nullptr;
+    g.eps = eps;
     return launch_gemm_bf16(EPI_QKV_ROPE, g, s);
   };
   HeadArgs ha{};
@@ -501,9 +504,13 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
     // projection reads it from the table instead (unless that layer is the
     // pruned last one, which gathers x rows)
     const bool x_from_table = p->n_layers > 1 || (p->n_layers == 1 && !prune);
+    LastDesc ld{};
+    if (prune) ld = LastDesc{at<int64_t>(ws, L.ldesc), last_blocks(seq_ub), last_rows(seq_ub)};
     TRACED(tr, AIQ_K_EMBED, launch_embed_norm(desc, cu, packed, m.emb, m.wdtype, d, m.vocab,
                                               x_from_table ? nullptr : x, pos, ctr, g0, eps,
-                                              h, p->act, rs, t_cap, s, pos_base));
+                                              h, p->act, rs, t_cap, s, pos_base, ld));
+    // small launches take row scales from the sums of squares where they are used
+    const bool fold = t_cap <= RS_FOLD_ROWS;
     const size_t pre_layer = static_cast<size_t>(pu.npre) * p->n_qkv * act_bytes(p);   // bytes per layer
     const size_t keep_layer = static_cast<size_t>(pu.qkv_rows) * p->n_qkv * act_bytes(p);
     for (int l = 0; l < p->n_layers; ++l) {
@@ -514,9 +521,10 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
         // keys and values for every position (columns d_q.. of the q|k|v rows)
         TRACED(tr, AIQ_K_GEMM_QKV, gemm_part(h, m_ptr, t_cap, 2 * p->d_kv, 0, p->d_kv, W.wq, W.wk, W.wv,
                                              static_cast<char*>(qkv_l) + static_cast<size_t>(p->d_q) * act_bytes(p),
-                                             p->n_qkv, rs, pos));
+                                             p->n_qkv, rs, pos, fold && l > 0));
       } else {
-        TRACED(tr, AIQ_K_GEMM_QKV, gemm(EPI_QKV_ROPE, h, d, p->n_qkv, d, W.wq, W.wk, W.wv, qkv_l, p->n_qkv));
+        TRACED(tr, AIQ_K_GEMM_QKV, gemm(EPI_QKV_ROPE, h, d, p->n_qkv, d, W.wq, W.wk, W.wv, qkv_l, p->n_qkv, nullptr,
+                                        nullptr, 0, nullptr, false, fold && l > 0));
       }
       AttnArgs aa{};
       aa.qkv = qkv_l;
@@ -542,18 +550,30 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
         int64_t* ldesc = at<int64_t>(ws, L.ldesc);
         float* xl = at<float>(ws, L.xl);
         const size_t hf_row = static_cast<size_t>(d) * (p->act ? 2 : 4);
-        TRACED(tr, AIQ_K_LAST, launch_last_desc(desc, ldesc, nb, R, s));
+        const bool fold_r = R <= RS_FOLD_ROWS;
         for (int32_t b = 0; b < nb; ++b) {
           const int64_t* bd = ldesc + static_cast<int64_t>(b) * D_STRIDE;
           GenAttnArgs ga{};
+          // the last positions' residual rows and, for their queries alone,
+          // their h rows, row scales and positions
+          LastRows lr{};
+          lr.x = x;
+          lr.xl = xl;
+          lr.d = d;
+          lr.eps = eps;
           if (p->q_last_only) {
-            // queries of the last positions: their h rows, row scales and
-            // positions gathered, then the q projection (rotary) into ffn
-            float* rsl = at<float>(ws, L.laux);
-            int32_t* posl = reinterpret_cast<int32_t*>(rsl + R + 256);
-            TRACED(tr, AIQ_K_LAST, launch_last_h(bd, cu, h, rs, pos, d, att, rsl, posl, R, s));
+            lr.h = h;
+            lr.rs = rs;
+            lr.ssp = fold && l > 0 ? ssp : nullptr;
+            lr.pos = pos;
+            lr.hl = att;
+            lr.rsl = at<float>(ws, L.laux);
+            lr.posl = reinterpret_cast<int32_t*>(lr.rsl + R + 256);
+          }
+          TRACED(tr, AIQ_K_LAST, launch_last_rows(bd, cu, lr, R, s));
+          if (p->q_last_only) {   // the q projection (rotary) into ffn
             TRACED(tr, AIQ_K_LAST, gemm_part(att, bd + D_NTOK, R, p->d_q, p->d_q, 0, W.wq, W.wk, W.wv, ffn, p->d_q,
-                                             rsl, posl));
+                                             lr.rsl, lr.posl, false));
             ga.qkv = ffn;
             ga.ldq = p->d_q;
           }
@@ -572,12 +592,11 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
           ga.seq_ub = R;
           ga.last_row = 1;
           TRACED(tr, AIQ_K_LAST, launch_attention_gen(ga, s));
-          TRACED(tr, AIQ_K_LAST, launch_last_rows(bd, cu, x, d, xl, R, s));
           TRACED(tr, AIQ_K_LAST, gemm(EPI_RESID, att, p->d_q, d, p->d_q, W.wo, nullptr, nullptr, nullptr, d,
                                       W.ffn_norm, bd + D_NTOK, R, xl));
-          TRACED(tr, AIQ_K_LAST, launch_row_scale(bd, ssp, d / 64, d, eps, rs, R, s));
+          if (!fold_r) TRACED(tr, AIQ_K_LAST, launch_row_scale(bd, ssp, d / 64, d, eps, rs, R, s));
           TRACED(tr, AIQ_K_LAST, gemm(EPI_SWIGLU, h, d, 2 * m.d_ff, d, W.w_gate, W.w_up, nullptr, ffn, m.d_ff,
-                                      nullptr, bd + D_NTOK, R));
+                                      nullptr, bd + D_NTOK, R, nullptr, false, fold_r));
           TRACED(tr, AIQ_K_LAST, gemm(EPI_RESID, ffn, m.d_ff, d, m.d_ff, W.w_down, nullptr, nullptr, nullptr, d,
                                       nullptr, bd + D_NTOK, R, xl));
           if (!pu.head) continue;
@@ -594,12 +613,13 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
       TRACED(tr, AIQ_K_ATTN, launch_attention_bf16(aa, s));
       TRACED(tr, AIQ_K_GEMM_O, gemm(EPI_RESID, att, p->d_q, d, p->d_q, W.wo, nullptr, nullptr, nullptr, d,
                                     W.ffn_norm, nullptr, 0, nullptr, l == 0 && x_from_table));
-      TRACED(tr, AIQ_K_NORM, launch_row_scale(desc, ssp, d / 64, d, eps, rs, t_cap, s));
-      TRACED(tr, AIQ_K_GEMM_UP, gemm(EPI_SWIGLU, h, d, 2 * m.d_ff, d, W.w_gate, W.w_up, nullptr, ffn, m.d_ff));
+      if (!fold) TRACED(tr, AIQ_K_NORM, launch_row_scale(desc, ssp, d / 64, d, eps, rs, t_cap, s));
+      TRACED(tr, AIQ_K_GEMM_UP, gemm(EPI_SWIGLU, h, d, 2 * m.d_ff, d, W.w_gate, W.w_up, nullptr, ffn, m.d_ff, nullptr,
+                                     nullptr, 0, nullptr, false, fold));
       // the head normalises the last position itself: after the last layer only x is needed
       TRACED(tr, AIQ_K_GEMM_DOWN, gemm(EPI_RESID, ffn, m.d_ff, d, m.d_ff, W.w_down, nullptr, nullptr, nullptr, d,
                                        last ? nullptr : p->layers[l + 1].attn_norm));
-      if (!last) TRACED(tr, AIQ_K_NORM, launch_row_scale(desc, ssp, d / 64, d, eps, rs, t_cap, s));
+      if (!last && !fold) TRACED(tr, AIQ_K_NORM, launch_row_scale(desc, ssp, d / 64, d, eps, rs, t_cap, s));
     }
   } else {
   TRACED(tr, AIQ_K_EMBED, launch_embed(desc, cu, packed, m.emb, m.wdtype, d, m.vocab, x, pos, ctr, t_cap, s));
@@ -650,7 +670,6 @@ aiq_status enqueue_generation(const aiq_plan* p, void* ws, const Layout& L, cons
   const int64_t su = p->seq_ub;
   int64_t* gd = at<int64_t>(ws, L.gdesc);
   int64_t* cnt = at<int64_t>(ws, L.gcnt);
-  int32_t* tok = at<int32_t>(ws, L.gtok);
   int32_t* done = at<int32_t>(ws, L.gdone);
   int32_t* gen = at<int32_t>(ws, L.gen);
   float* logits = at<float>(ws, L.glog);
@@ -669,7 +688,7 @@ aiq_status enqueue_generation(const aiq_plan* p, void* ws, const Layout& L, cons
   TRACED(tr, AIQ_K_DECODE, launch_fill_i32(done, su, 0, s));
   auto gemm = [&](int epi, const void* A, int64_t lda, const int64_t* m_ptr, int64_t m_ub, int N, int K,
                   const void* B0, const void* B1, const void* B2, void* C, int64_t ldc, const float* gnext,
-                  bool resid) {
+                  bool resid, bool from_ssp = false) {
     GemmArgs g{};
     g.A = A;
     g.lda = lda;
@@ -689,6 +708,8 @@ aiq_status enqueue_generation(const aiq_plan* p, void* ws, const Layout& L, cons
     g.rope_rev = at<float>(ws, L.rrev);
     g.f16 = p->act == 2;
     g.rs = rs;
+    g.ssp_in = from_ssp ? ssp : nullptr;
+    g.eps = eps;
     if (resid) {
       g.x = x;
       g.gnext = gnext;
@@ -698,33 +719,57 @@ aiq_status enqueue_generation(const aiq_plan* p, void* ws, const Layout& L, cons
     }
     return launch_gemm_bf16(epi, g, s);
   };
-  // full-vocabulary head over hf in row blocks, argmax into generated slot `step`
-  auto next_tokens = [&](int step) -> aiq_status {
+  const bool fold = su <= RS_FOLD_ROWS;   // row scales taken where they are used
+  const float* g0 = p->n_layers > 0 ? p->layers[0].attn_norm : m.final_norm;
+  // full-vocabulary head over rows of `src` in blocks, argmax into generated
+  // slot `step`, the embedding of the next step's row.  A row's scale does not
+  // change its argmax: the steps' rows are the final norm's operand x * g.
+  auto next_tokens = [&](int step, const void* src) -> aiq_status {
     for (int b = 0; b < p->gen_blocks; ++b) {
       const int64_t row0 = static_cast<int64_t>(b) * GEN_HEAD_ROWS;
-      TRACED(tr, AIQ_K_DECODE_HEAD, gemm(EPI_ARGMAX, static_cast<const char*>(hf) + row0 * d * ab, d, cnt + b,
+      TRACED(tr, AIQ_K_DECODE_HEAD, gemm(EPI_ARGMAX, static_cast<const char*>(src) + row0 * d * ab, d, cnt + b,
                                          std::min<int64_t>(su - row0, GEN_HEAD_ROWS), m.vocab, d, m.lm_head,
                                          nullptr, nullptr, logits, m.vocab / 64, nullptr, false));
-      TRACED(tr, AIQ_K_DECODE_HEAD, launch_gen_argmax(logits, m.vocab, cnt + b, row0, gd, step, G, q.eos_id, q.pad_id,
-                                                 tok, done, gen, s));
+      GenNextArgs na{};
+      na.part = logits;
+      na.vocab = m.vocab;
+      na.cnt = cnt + b;
+      na.row0 = row0;
+      na.gen_desc = gd;
+      na.step = step;
+      na.G = G;
+      na.eos = q.eos_id;
+      na.pad = q.pad_id;
+      na.done = done;
+      na.gen = gen;
+      na.cu = cu;
+      na.npre = npre;
+      na.emb = m.emb;
+      na.wdtype = m.wdtype;
+      na.d = d;
+      na.x = x;
+      na.pos = pos;
+      na.g = g0;
+      na.eps = eps;
+      na.h = h;
+      na.h_act = p->act;
+      na.rs = rs;
+      TRACED(tr, AIQ_K_DECODE_HEAD, launch_gen_next(na, s));
     }
     return AIQ_OK;
   };
-  aiq_status e = next_tokens(0);
+  aiq_status e = next_tokens(0, hf);
   if (e != AIQ_OK) return e;
   const int64_t* n_rows = gd + D_NTOK;
   const size_t kv_layer = static_cast<size_t>(pu.qkv_rows) * p->n_qkv * ab;
   const size_t pre_layer = static_cast<size_t>(npre) * p->n_qkv * ab;
   const size_t gkv_layer = static_cast<size_t>(su) * G * 2 * p->d_kv * ab;
-  const float* g0 = p->n_layers > 0 ? p->layers[0].attn_norm : m.final_norm;
   for (int k = 0; k + 1 < G; ++k) {
-    TRACED(tr, AIQ_K_DECODE, launch_gen_embed(gd, cu, tok, k, npre, m.emb, m.wdtype, d, m.vocab, x, pos, g0, eps, h,
-                                              p->act, rs, su, s));
     for (int l = 0; l < p->n_layers; ++l) {
       const aiq_layer& W = p->layers[l];
       const bool last = l + 1 == p->n_layers;
       TRACED(tr, AIQ_K_DECODE, gemm(EPI_QKV_ROPE, h, d, n_rows, su, p->n_qkv, d, W.wq, W.wk, W.wv, qkv, p->n_qkv,
-                                    nullptr, false));
+                                    nullptr, false, fold && l > 0));
       GenAttnArgs ga{};
       ga.qkv = qkv;
       ga.kvc = static_cast<const char*>(pu.qkv_layers) + l * kv_layer;
@@ -746,15 +791,14 @@ aiq_status enqueue_generation(const aiq_plan* p, void* ws, const Layout& L, cons
       TRACED(tr, AIQ_K_DECODE_ATTN, launch_attention_gen(ga, s));
       TRACED(tr, AIQ_K_DECODE, gemm(EPI_RESID, att, p->d_q, n_rows, su, d, p->d_q, W.wo, nullptr, nullptr, nullptr,
                                     d, W.ffn_norm, true));
-      TRACED(tr, AIQ_K_DECODE, launch_row_scale(gd, ssp, d / 64, d, eps, rs, su, s));
+      if (!fold) TRACED(tr, AIQ_K_DECODE, launch_row_scale(gd, ssp, d / 64, d, eps, rs, su, s));
       TRACED(tr, AIQ_K_DECODE, gemm(EPI_SWIGLU, h, d, n_rows, su, 2 * m.d_ff, d, W.w_gate, W.w_up, nullptr, ffn,
-                                    m.d_ff, nullptr, false));
+                                    m.d_ff, nullptr, false, fold));
       TRACED(tr, AIQ_K_DECODE, gemm(EPI_RESID, ffn, m.d_ff, n_rows, su, d, m.d_ff, W.w_down, nullptr, nullptr,
-                                    nullptr, d, last ? nullptr : p->layers[l + 1].attn_norm, true));
-      if (!last) TRACED(tr, AIQ_K_DECODE, launch_row_scale(gd, ssp, d / 64, d, eps, rs, su, s));
+                                    nullptr, d, last ? m.final_norm : p->layers[l + 1].attn_norm, true));
+      if (!last && !fold) TRACED(tr, AIQ_K_DECODE, launch_row_scale(gd, ssp, d / 64, d, eps, rs, su, s));
     }
-    TRACED(tr, AIQ_K_DECODE, launch_norm_rows(gd, x, m.final_norm, d, eps, hf, p->act, su, s));
-    e = next_tokens(k + 1);
+    e = next_tokens(k + 1, h);
     if (e != AIQ_OK) return e;
   }
   return AIQ_OK;
@@ -1116,9 +1160,11 @@ aiq_status aiq_run(const aiq_plan* p, void* ws, size_t ws_bytes, const aiq_out* 
   if (!p->pairs)
     HIP_TRY(launch_gather_tokens(sel, ctr + C_SEL, n, p->probe.list_offsets, p->probe.list_tokens, cu, row_prefix,
                                  p->model.vocab, p->t_ub, packed, ctr, s));
-  HIP_TRY(launch_chunk_desc(cu, n_seq, p->chunk_tokens, p->n_chunks, p->t_ub, desc, s));
-  HIP_TRY(launch_rope_table(p->max_seq, p->hd / 2, p->model.rope_theta, p->hd, at<float>(ws, L.rcos),
-                            at<float>(ws, L.rsin), at<float>(ws, L.rrev), s));
+  const RopeRev rr{p->bf16 ? at<float>(ws, L.rrev) : nullptr, p->hd, p->model.rope_theta};
+  HIP_TRY(launch_chunk_desc(cu, n_seq, p->chunk_tokens, p->n_chunks, p->t_ub, desc, rr, s));
+  if (!p->bf16)
+    HIP_TRY(launch_rope_table(p->max_seq, p->hd / 2, p->model.rope_theta, p->hd, at<float>(ws, L.rcos),
+                              at<float>(ws, L.rsin), s));
   tr.end();
   // ---- shared prompt prefix: its own prefill pass keeps every layer's q|k|v rows
   PrefixUse rows_pu{};
@@ -1324,10 +1370,11 @@ aiq_status aiq_prefill_packed(const aiq_plan* p, const int32_t* tok, const int32
   int64_t* ctr = at<int64_t>(ws, L.ctr);
   int64_t* desc = at<int64_t>(ws, L.desc);
   int64_t* cu = at<int64_t>(ws, L.cu);
-  HIP_TRY(launch_fill_i64(ctr, C_COUNT, 0, s));
-  HIP_TRY(launch_packed_desc(cu_seqlens, n_seq, n_tok, cu, desc, ctr, s));
-  HIP_TRY(launch_rope_table(static_cast<int32_t>(std::min<int64_t>(cap, INT32_MAX)), p->hd / 2, p->model.rope_theta,
-                            p->hd, at<float>(ws, L.rcos), at<float>(ws, L.rsin), at<float>(ws, L.rrev), s));
+  const RopeRev rr{p->bf16 ? at<float>(ws, L.rrev) : nullptr, p->hd, p->model.rope_theta};
+  HIP_TRY(launch_packed_desc(cu_seqlens, n_seq, n_tok, cu, desc, ctr, rr, s));
+  if (!p->bf16)   // positions stay below the batch's tokens
+    HIP_TRY(launch_rope_table(static_cast<int32_t>(std::min<int64_t>(n_tok, INT32_MAX)), p->hd / 2,
+                              p->model.rope_theta, p->hd, at<float>(ws, L.rcos), at<float>(ws, L.rsin), s));
   const bool full = logits_mode == AIQ_LOGITS_FULL_VOCAB;
   void* hf = full ? at<void>(ws, L.hf) : nullptr;
   int32_t* label = at<int32_t>(ws, L.label);

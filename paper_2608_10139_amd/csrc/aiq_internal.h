@@ -189,13 +189,21 @@ hipError_t launch_gather_tokens(const int32_t* sel, const int64_t* n_ptr, int64_
                                 const int64_t* offsets, const int32_t* tokens, const int64_t* cu,
                                 const Prefix& prefix, int32_t vocab, int64_t t_ub, int32_t* packed,
                                 int64_t* ctr, hipStream_t s);
+// Rotary frequencies of the MFMA path, rev[i] = theta^(-2i/hd) / (2 pi) for
+// i < hd / 2, written beside the descriptors (rev null: not written).
+struct RopeRev {
+  float* rev;
+  int32_t hd;
+  double theta;
+};
 // Chunk c: the sequences i with cu[i] + i in [c, c + 1) * chunk_tokens (at
 // most chunk_tokens sequences per chunk, empty lists included); the last
 // chunk runs to the last sequence.
 hipError_t launch_chunk_desc(const int64_t* cu, const int64_t* n_ptr, int64_t chunk_tokens,
-                             int64_t n_chunks, int64_t t_ub, int64_t* desc, hipStream_t s);
+                             int64_t n_chunks, int64_t t_ub, int64_t* desc, const RopeRev& rr, hipStream_t s);
+// also clears the counters ctr[0..C_COUNT)
 hipError_t launch_packed_desc(const int32_t* cu32, int32_t n_seq, int64_t n_tok, int64_t* cu64,
-                              int64_t* desc, int64_t* ctr, hipStream_t s);
+                              int64_t* desc, int64_t* ctr, const RopeRev& rr, hipStream_t s);
 // The shared prompt prefix as a one-sequence batch: tok[0..n) = prefix,
 // cu = {0, n}, desc = one chunk of n tokens.
 hipError_t launch_prefix_batch(const Prefix& prefix, int32_t* tok, int64_t* cu, int64_t* desc, hipStream_t s);
@@ -205,9 +213,9 @@ hipError_t launch_bf16_to_f16(const void* src, void* dst, int64_t n, hipStream_t
 hipError_t launch_copy_row_f32(const float* src, float* dst, int32_t n, hipStream_t s);
 
 // per-chunk transformer
-// cos/sin table [max_pos, hd/2] and the per-dim frequency in revolutions [hd/2]
+// cos/sin table [max_pos, hd/2] (fp32 path)
 hipError_t launch_rope_table(int32_t max_pos, int32_t half, double theta, int32_t hd, float* cos_t,
-                             float* sin_t, float* rev, hipStream_t s);
+                             float* sin_t, hipStream_t s);
 hipError_t launch_embed(const int64_t* desc, const int64_t* cu, const int32_t* packed,
                         const void* emb, int32_t wdtype, int32_t d, int32_t vocab, float* x, int32_t* pos,
                         int64_t* ctr, int64_t t_cap, hipStream_t s);
@@ -216,12 +224,23 @@ hipError_t launch_embed(const int64_t* desc, const int64_t* cu, const int32_t* p
 // pos_base is added to every position (the row tokens that follow a shared
 // prefix start at the prefix length).  x may be null: the residual is then
 // not written (the first layer's O projection reads the embedding rows).
+// last (blocks > 0): the descriptors of the chunk's last positions as well.
+struct LastDesc {
+  int64_t* ldesc;   // block b < blocks covers local sequences [b R, min(n, (b + 1) R)):
+  int32_t blocks;   // ldesc[b] = {chunk's first token, rows, chunk's first sequence + b R, rows}
+  int64_t R;
+};
 hipError_t launch_embed_norm(const int64_t* desc, const int64_t* cu, const int32_t* packed, const void* emb,
                              int32_t wdtype, int32_t d, int32_t vocab, float* x, int32_t* pos, int64_t* ctr,
                              const float* g, float eps, void* h, int32_t h_act, float* rs, int64_t t_cap,
-                             hipStream_t s, int32_t pos_base = 0);
+                             hipStream_t s, int32_t pos_base = 0, LastDesc last = LastDesc{});
 // rs[t] = 1 / sqrt(sum_p ssp[t, p] / d + eps) for the chunk's tokens, the
 // partial sums added in order p = 0, 1, ...
+// Launches of at most RS_FOLD_ROWS rows leave it to the projection that
+// consumes the scales (GemmArgs::ssp_in): a launch of its own costs 2.6-4.8 us,
+// reading the sums in each tile about 1.  Above, projections may take 256-row tiles,
+// which have no registers left for it.
+constexpr int64_t RS_FOLD_ROWS = 1024;
 hipError_t launch_row_scale(const int64_t* desc, const float* ssp, int32_t n_part, int32_t d, float eps,
                             float* rs, int64_t t_cap, hipStream_t s);
 // x += delta (when delta is non-null, written back), then out = RMSNorm(x) * g
@@ -257,6 +276,8 @@ struct GemmArgs {
   int32_t f16;               // MFMA path: operands are fp16 (else bf16)
   // Residual stream with the RMSNorm folded into the projections (MFMA path):
   const float* rs;           // EPI_QKV_ROPE / EPI_SWIGLU: per-row scale 1/rms (rows padded by 256), or null
+  const float* ssp_in;       // ... or, where set, the row's sums of squares [M, K / 64] it is taken from (then no 256-row tiles)
+  float eps;                 // (as launch_row_scale)
   float* x;                  // EPI_RESID: residual [M, ldc] fp32, x += A.W^T in place
   const float* gnext;        // EPI_RESID: gain of the RMSNorm that follows (null: only x is written)
   void* hout;                // EPI_RESID: [M, ldc] 16-bit, x * gnext (the next projection's operand)
@@ -374,13 +395,6 @@ hipError_t launch_pair_rows(const int32_t* ids, const int64_t* n_ptr, int64_t n_
 constexpr int GEN_HEAD_ROWS = 4096;
 hipError_t launch_gen_desc(const int64_t* chunk_desc, int64_t* gen_desc, int64_t* cnt, int32_t n_blocks,
                            hipStream_t s);
-// Embedding of each sequence's current token at position (its prompt
-// length incl. a shared prefix of npre tokens) + step, with the first norm's
-// operand h = x * g and row scale rs (as launch_embed_norm).
-hipError_t launch_gen_embed(const int64_t* gen_desc, const int64_t* cu, const int32_t* tok, int32_t step,
-                            int32_t npre, const void* emb, int32_t wdtype, int32_t d, int32_t vocab, float* x,
-                            int32_t* pos, const float* g, float eps, void* h, int32_t h_act, float* rs,
-                            int64_t seq_ub, hipStream_t s);
 struct GenAttnArgs {
   const void* qkv;           // [n, ld] this step's q|k|v, one row per sequence
   const void* kvc;           // the chunk's prompt rows for this layer, [chunk tokens, ld] q|k|v
@@ -403,29 +417,54 @@ struct GenAttnArgs {
   int64_t ldq;
 };
 hipError_t launch_attention_gen(const GenAttnArgs& a, hipStream_t s);
-// Descriptors of the last positions of a chunk's sequences in blocks of R:
-// block b (b < nb) covers local sequences [b R, min(n, (b + 1) R)):
-// ldesc[b] = {chunk's first token, rows, chunk's first sequence + b R, rows}.
-hipError_t launch_last_desc(const int64_t* chunk_desc, int64_t* ldesc, int32_t nb, int64_t R, hipStream_t s);
-// The last position of sequence i (i < ldesc[D_NSEQ]): its 16-bit
-// normalised row h (d values), row scale and position, into row i of hl, rsl
-// and posl; sequences with no own row are left as they are.
-hipError_t launch_last_h(const int64_t* ldesc, const int64_t* cu, const void* h, const float* rs, const int32_t* pos,
-                         int32_t d, void* hl, float* rsl, int32_t* posl, int64_t R, hipStream_t s);
-// xl[i] = x[last row of sequence i] (fp32 rows of d), i < ldesc[D_NSEQ];
-// sequences with no own row are left as they are.
-hipError_t launch_last_rows(const int64_t* ldesc, const int64_t* cu, const float* x, int32_t d, float* xl,
-                            int64_t R, hipStream_t s);
-// hf[i] = x[i] / rms * g in 16 bits, i < gen_desc[D_NSEQ]
-hipError_t launch_norm_rows(const int64_t* gen_desc, const float* x, const float* g, int32_t d, float eps, void* hf,
-                            int32_t act, int64_t seq_ub, hipStream_t s);
+// The last position of sequence i (i < ldesc[D_NSEQ]): its residual row x (d
+// fp32 values) into row i of xl and, with hl, its 16-bit normalised row h, row
+// scale and position into row i of hl, rsl and posl; the scale from rs, or with ssp
+// from the row's sums of squares (as launch_row_scale).  Sequences with no own
+// row are left as they are.
+struct LastRows {
+  const float* x;
+  float* xl;
+  const void* h;
+  const float* rs;
+  const float* ssp;
+  const int32_t* pos;
+  int32_t d;
+  float eps;
+  void* hl;
+  float* rsl;
+  int32_t* posl;
+};
+hipError_t launch_last_rows(const int64_t* ldesc, const int64_t* cu, const LastRows& a, int64_t R, hipStream_t s);
 // Argmax over a block of full-vocabulary rows given as the head GEMM's
 // EPI_ARGMAX partials (int2 [rows][vocab / 64]; ties to the lowest id):
 // row r is sequence i = row0 + r; its token goes to gen[(seq_begin + i) * G +
-// step] (pad_id once the sequence has ended), tok[i] and done[i].
-hipError_t launch_gen_argmax(const void* part, int32_t vocab, const int64_t* cnt, int64_t row0,
-                             const int64_t* gen_desc, int32_t step, int32_t G, int32_t eos, int32_t pad,
-                             int32_t* tok, int32_t* done, int32_t* gen, hipStream_t s);
+// step] (pad_id once the sequence has ended) and done[i].  Unless it is the
+// last step the row's embedding follows at once: x = E[token], the first norm's
+// operand h = x * g and row scale rs (as launch_embed_norm), and the position
+// (prompt length incl. a shared prefix of npre tokens, + step).
+struct GenNextArgs {
+  const void* part;
+  int32_t vocab;
+  const int64_t* cnt;        // rows of the block
+  int64_t row0;
+  const int64_t* gen_desc;
+  int32_t step, G, eos, pad;
+  int32_t* done;
+  int32_t* gen;
+  const int64_t* cu;
+  int32_t npre;
+  const void* emb;
+  int32_t wdtype, d;
+  float* x;
+  int32_t* pos;
+  const float* g;
+  float eps;
+  void* h;
+  int32_t h_act;
+  float* rs;
+};
+hipError_t launch_gen_next(const GenNextArgs& a, hipStream_t s);
 struct LikePattern {
   int32_t n;
   int32_t tok[AIQ_MAX_LIKE];

@@ -22,4 +22,19 @@ __device__ __forceinline__ float h2f(uint16_t h) { return static_cast<float>(__b
 __device__ __forceinline__ uint16_t f2act(float f, int act) { return act == ACT_F16 ? f2h(f) : f2bf(f); }
 __device__ __forceinline__ float act2f(uint16_t v, int act) { return act == ACT_F16 ? h2f(v) : bf2f(v); }
 
+// RMSNorm scale of a row from its n_part sums of squares (n_part % 4 == 0,
+// 16-byte aligned), added in order.
+__device__ __forceinline__ float row_scale(const float* p, int n_part, int d, float eps) {
+  float ss = 0.f;
+#pragma unroll 4
+  for (int k = 0; k < n_part; k += 4) {
+    const float4 v = *reinterpret_cast<const float4*>(p + k);
+    ss += v.x;
+    ss += v.y;
+    ss += v.z;
+    ss += v.w;
+  }
+  return 1.0f / sqrtf(ss / static_cast<float>(d) + eps);
+}
+
 }  // namespace aiq

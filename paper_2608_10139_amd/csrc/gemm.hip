@@ -605,7 +605,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, int64_t M, uint16_
         }
       }
     }
-    if (PAIR && a.rs && t < BM) rbuf[t] = a.rs[m0 + t];   // padded by 256 rows
+    if (PAIR && t < BM) {
+      if (a.ssp_in)
+        rbuf[t] = row_scale(a.ssp_in + (m0 + (t < rows ? t : 0)) * (a.K / 64), a.K / 64, a.K, a.eps);
+      else if (a.rs)
+        rbuf[t] = a.rs[m0 + t];   // padded by 256 rows
+    }
     if (RESID && a.gnext && t < BN) rbuf[t] = a.gnext[n0 + t];
     if (EPI == EPI_QKV_ROPE && t < BM) pbuf[t] = a.pos[m0 + t];
 
@@ -727,7 +732,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, int64_t M, uint16_
 #pragma unroll
       for (int u = 0; u < BM * QPR / GT; ++u) {
         const int p = t + u * GT, r = p / QPR, h = (p % QPR) >> 2, q = p & 3;
-        const float rs = a.rs ? rbuf[r] : 1.f;
+        const float rs = a.rs || a.ssp_in ? rbuf[r] : 1.f;
         const float4 l0 = rd(r, 16 * h + 2 * q), l1 = rd(r, 16 * h + 2 * q + 1);
         const float4 u0 = rd(r, 16 * h + 2 * q + 8), u1 = rd(r, 16 * h + 2 * q + 9);
         if (r < rows) pair_piece<EPI, H>(a, l0, l1, u0, u1, rs, n0 + 64 * h, q, m0 + r, pbuf[r], rvbuf);
@@ -742,13 +747,14 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, int64_t M, uint16_
 // weights: 64 x 64 tiles 0.21 / 2.2 (10 us at K = 2048, 30 at 8192), 128 x 128
 // 0.53 / 4.5 (21, 69), 256 x 256 1.44 / 11 (60, 196; the maxima epilogue
 // takes 40).  The 256-row tiles' rounds count by XCD, whose rows they are
-// dealt to in turn.  They also need a whole tile of rows (tile_sources).
+// dealt to in turn.  They also need a whole tile of rows (tile_sources) and row
+// scales, not sums (`large`).
 // Measured at K = 3072, N = 3072: M = 120 17 us against 92 with the large
 // tiles only, M = 800 37 against 91, M = 1920 70 against 91, M = 3300 112
 // against 93.
 enum TilePath : int { PATH_256 = 0, PATH_128 = 1, PATH_64 = 2 };
 template <int EPI>
-__device__ __forceinline__ int tile_path(int64_t M, int N, int K, int wgs) {
+__device__ __forceinline__ int tile_path(int64_t M, int N, int K, int wgs, bool large) {
   auto rounds = [](int64_t tiles, int slots) { return static_cast<float>((tiles + slots - 1) / slots); };
   auto tiles = [&](int b) { return ((M + b - 1) / b) * (N / b); };
   const float k = static_cast<float>(K / GK);
@@ -756,7 +762,7 @@ __device__ __forceinline__ int tile_path(int64_t M, int N, int K, int wgs) {
   const float c128 = rounds(tiles(128), wgs) * (0.53f * k + 4.5f);
   const int64_t rows_x = ((M + GM - 1) / GM + 7) / 8;
   const float c256 = rounds(rows_x * (N / GN), wgs >> 3) * (1.44f * k + (EPI == EPI_ARGMAX ? 40.f : 11.f));
-  if (M >= GM && c256 <= c128 && c256 <= c64) return PATH_256;
+  if (large && M >= GM && c256 <= c128 && c256 <= c64) return PATH_256;
   return c128 < c64 ? PATH_128 : PATH_64;
 }
 
@@ -777,7 +783,7 @@ __global__ __launch_bounds__(GT, 1) void k_gemm_bf16(GemmArgs a) {
   const int64_t tok0 = EPI == EPI_RESID_EMB ? a.x_tok_desc[D_TOK_BEGIN] : 0;   // the rows' first packed token
   if (EPI == EPI_QKV_ROPE && static_cast<int>(threadIdx.x) < (a.hd >> 1))
     rvbuf[threadIdx.x] = a.rope_rev[threadIdx.x];   // visible after the first barrier
-  const int path = tile_path<EPI>(M, a.N, a.K, gridDim.x);
+  const int path = tile_path<EPI>(M, a.N, a.K, gridDim.x, !a.ssp_in);
   if (path == PATH_64) return gemm_tiles<EPI, H, 64, 64, 2>(a, M, sA0, sB0, sA1, sB1, rbuf, pbuf, rvbuf);
   if (path == PATH_128) return gemm_tiles<EPI, H, 128, 128, 1>(a, M, sA0, sB0, sA1, sB1, rbuf, pbuf, rvbuf);
   const int tiles_n = a.N / GN;
@@ -878,6 +884,7 @@ __global__ __launch_bounds__(GT, 1) void k_gemm_bf16(GemmArgs a) {
 
 hipError_t launch_gemm_bf16(int epi, const GemmArgs& a, hipStream_t s) {
   if (a.K <= 0 || a.K % (2 * GK) || a.N % GN) return hipErrorInvalidValue;   // whole pairs of k-steps, whole tiles
+  if (a.ssp_in && a.K % 256) return hipErrorInvalidValue;                    // sums read four at a time
   // one workgroup per CU, rounded to whole XCD groups; fewer for small problems
   const int64_t tiles = ((a.m_ub + 63) / 64) * (a.N / 64);   // the smallest tiles
   int64_t g = num_cus();

@@ -54,126 +54,35 @@ hipError_t launch_gen_desc(const int64_t* chunk_desc, int64_t* gen_desc, int64_t
 // The label head needs only each sequence's last position, and in the last
 // layer nothing after the q|k|v projection feeds any other position: that
 // layer's attention (for the last query), O projection, norm and FFN run on
-// one row per sequence, in blocks of R sequences.
-__global__ void k_last_desc(const int64_t* cd, int64_t* ld, int32_t nb, int64_t R) {
-  const int64_t n = cd[D_NSEQ];
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) {
-    int64_t r = n - static_cast<int64_t>(b) * R;
-    r = r < 0 ? 0 : (r > R ? R : r);
-    int64_t* o = ld + static_cast<int64_t>(b) * D_STRIDE;
-    o[D_TOK_BEGIN] = cd[D_TOK_BEGIN];
-    o[D_NTOK] = r;
-    o[D_SEQ_BEGIN] = cd[D_SEQ_BEGIN] + static_cast<int64_t>(b) * R;
-    o[D_NSEQ] = r;
-  }
-}
-
-hipError_t launch_last_desc(const int64_t* chunk_desc, int64_t* ldesc, int32_t nb, int64_t R, hipStream_t s) {
-  if (nb <= 0 || R <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_last_desc, dim3(1), dim3(256), 0, s, chunk_desc, ldesc, nb, R);
-  return hipGetLastError();
-}
-
-// Wave per sequence, 16-byte pieces of the row.
-__global__ __launch_bounds__(256) void k_last_rows(const int64_t* ld, const int64_t* cu, const float* x, int32_t d,
-                                                   float* xl) {
+// one row per sequence, in blocks of R sequences.  Wave per sequence, 16-byte
+// pieces of its rows.
+__global__ __launch_bounds__(256) void k_last_rows(const int64_t* ld, const int64_t* cu, LastRows a) {
   const int64_t n = ld[D_NSEQ], sb = ld[D_SEQ_BEGIN], tb = ld[D_TOK_BEGIN];
   const int lane = threadIdx.x & 63;
   const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t i = wave; i < n; i += n_waves) {
-    const int64_t c1 = cu[sb + i + 1];
-    if (c1 == cu[sb + i]) continue;
-    const float4* src = reinterpret_cast<const float4*>(x + (c1 - 1 - tb) * d);
-    float4* dst = reinterpret_cast<float4*>(xl + i * d);
-    for (int c = lane; c < d / 4; c += 64) dst[c] = src[c];
-  }
-}
-
-// Wave per sequence: the row of d 16-bit values in 16-byte pieces.
-__global__ __launch_bounds__(256) void k_last_h(const int64_t* ld, const int64_t* cu, const uint16_t* h,
-                                                const float* rs, const int32_t* pos, int32_t d, uint16_t* hl,
-                                                float* rsl, int32_t* posl) {
-  const int64_t n = ld[D_NSEQ], sb = ld[D_SEQ_BEGIN], tb = ld[D_TOK_BEGIN];
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  const int d = a.d;
   for (int64_t i = wave; i < n; i += n_waves) {
     const int64_t c1 = cu[sb + i + 1];
     if (c1 == cu[sb + i]) continue;
     const int64_t r = c1 - 1 - tb;
-    const uint4* src = reinterpret_cast<const uint4*>(h + r * d);
-    uint4* dst = reinterpret_cast<uint4*>(hl + i * d);
-    for (int c = lane; c < d / 8; c += 64) dst[c] = src[c];
+    const float4* src = reinterpret_cast<const float4*>(a.x + r * d);
+    float4* dst = reinterpret_cast<float4*>(a.xl + i * d);
+    for (int c = lane; c < d / 4; c += 64) dst[c] = src[c];
+    if (!a.hl) continue;
+    const uint4* hs = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.h) + r * d);
+    uint4* hd = reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.hl) + i * d);
+    for (int c = lane; c < d / 8; c += 64) hd[c] = hs[c];
     if (lane == 0) {
-      rsl[i] = rs[r];
-      posl[i] = pos[r];
+      a.rsl[i] = a.ssp ? row_scale(a.ssp + r * (d / 64), d / 64, d, a.eps) : a.rs[r];
+      a.posl[i] = a.pos[r];
     }
   }
 }
 
-hipError_t launch_last_h(const int64_t* ldesc, const int64_t* cu, const void* h, const float* rs, const int32_t* pos,
-                         int32_t d, void* hl, float* rsl, int32_t* posl, int64_t R, hipStream_t s) {
-  if (d % 8) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_last_h, dim3(grid_for(R, 4, 8192)), dim3(256), 0, s, ldesc, cu,
-                     static_cast<const uint16_t*>(h), rs, pos, d, static_cast<uint16_t*>(hl), rsl, posl);
-  return hipGetLastError();
-}
-
-hipError_t launch_last_rows(const int64_t* ldesc, const int64_t* cu, const float* x, int32_t d, float* xl,
-                            int64_t R, hipStream_t s) {
-  if (d % 4) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_last_rows, dim3(grid_for(R, 4, 8192)), dim3(256), 0, s, ldesc, cu, x, d, xl);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ embedding of the current tokens
-// Wave per sequence: x = E[tok], h = x * g (16-bit), rs = 1 / rms(x), and the
-// position after the prompt (shared prefix included) and the earlier steps.
-__global__ __launch_bounds__(256) void k_gen_embed(const int64_t* gd, const int64_t* cu, const int32_t* tok,
-                                                   int32_t step, int32_t npre, const uint16_t* emb, int32_t ea,
-                                                   int32_t d, int32_t vocab, float* x, int32_t* pos, const float* g,
-                                                   float eps, uint16_t* h, int32_t h_act, float* rs) {
-  const int64_t n = gd[D_NSEQ], sb = gd[D_SEQ_BEGIN];
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t i = wave; i < n; i += n_waves) {
-    int32_t t = tok[i];
-    if (t < 0 || t >= vocab) t = 0;   // argmax ids are in range; keeps the gather in bounds regardless
-    if (lane == 0) pos[i] = npre + static_cast<int32_t>(cu[sb + i + 1] - cu[sb + i]) + step;
-    const uint16_t* er = emb + static_cast<int64_t>(t) * d;
-    float* xr = x + i * d;
-    float ssq = 0.f;
-    for (int c = lane * 4; c < d; c += 256) {
-      const uint2 v = *reinterpret_cast<const uint2*>(er + c);
-      float4 o;
-      o.x = act2f(static_cast<uint16_t>(v.x & 0xFFFFu), ea);
-      o.y = act2f(static_cast<uint16_t>(v.x >> 16), ea);
-      o.z = act2f(static_cast<uint16_t>(v.y & 0xFFFFu), ea);
-      o.w = act2f(static_cast<uint16_t>(v.y >> 16), ea);
-      *reinterpret_cast<float4*>(xr + c) = o;
-      const float4 gv = *reinterpret_cast<const float4*>(g + c);
-      uint2 hv;
-      hv.x = f2act(o.x * gv.x, h_act) | (static_cast<uint32_t>(f2act(o.y * gv.y, h_act)) << 16);
-      hv.y = f2act(o.z * gv.z, h_act) | (static_cast<uint32_t>(f2act(o.w * gv.w, h_act)) << 16);
-      *reinterpret_cast<uint2*>(h + i * d + c) = hv;
-      ssq += (o.x * o.x + o.y * o.y) + (o.z * o.z + o.w * o.w);
-    }
-    ssq = wave_sum_g(ssq);
-    if (lane == 0) rs[i] = 1.0f / sqrtf(ssq / static_cast<float>(d) + eps);
-  }
-}
-
-hipError_t launch_gen_embed(const int64_t* gen_desc, const int64_t* cu, const int32_t* tok, int32_t step,
-                            int32_t npre, const void* emb, int32_t wdtype, int32_t d, int32_t vocab, float* x,
-                            int32_t* pos, const float* g, float eps, void* h, int32_t h_act, float* rs,
-                            int64_t seq_ub, hipStream_t s) {
-  if ((wdtype != AIQ_BF16 && wdtype != AIQ_F16) || h_act == ACT_F32 || d % 4) return hipErrorInvalidValue;
-  const int ea = wdtype == AIQ_F16 ? ACT_F16 : ACT_BF16;
-  hipLaunchKernelGGL(k_gen_embed, dim3(grid_for(seq_ub, 4, 8192)), dim3(256), 0, s, gen_desc, cu, tok, step, npre,
-                     static_cast<const uint16_t*>(emb), ea, d, vocab, x, pos, g, eps, static_cast<uint16_t*>(h),
-                     h_act, rs);
+hipError_t launch_last_rows(const int64_t* ldesc, const int64_t* cu, const LastRows& a, int64_t R, hipStream_t s) {
+  if (a.d % 8 || (a.hl && (!a.h || (!a.rs && !a.ssp) || (a.ssp && a.d % 256)))) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_last_rows, dim3(grid_for(R, 4, 8192)), dim3(256), 0, s, ldesc, cu, a);
   return hipGetLastError();
 }
 
@@ -431,45 +340,22 @@ hipError_t launch_attention_gen(const GenAttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ final norm of the step rows
-__global__ __launch_bounds__(256) void k_norm_rows(const int64_t* gd, const float* x, const float* g, int32_t d,
-                                                   float eps, uint16_t* hf, int32_t act) {
-  const int64_t n = gd[D_NSEQ];
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t i = wave; i < n; i += n_waves) {
-    const float* xr = x + i * d;
-    float ss = 0.f;
-    for (int c = lane; c < d; c += 64) ss += xr[c] * xr[c];
-    ss = wave_sum_g(ss);
-    const float r = 1.0f / sqrtf(ss / static_cast<float>(d) + eps);
-    for (int c = lane; c < d; c += 64) hf[i * d + c] = f2act(xr[c] * r * g[c], act);
-  }
-}
-
-hipError_t launch_norm_rows(const int64_t* gen_desc, const float* x, const float* g, int32_t d, float eps, void* hf,
-                            int32_t act, int64_t seq_ub, hipStream_t s) {
-  if (act == ACT_F32) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_norm_rows, dim3(grid_for(seq_ub, 4, 4096)), dim3(256), 0, s, gen_desc, x, g, d, eps,
-                     static_cast<uint16_t*>(hf), act);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ argmax of the next token
+// ------------------------------------------------------------------ the next token and its embedding
 // The head GEMM leaves, per row, the maximum and its column over every 64
 // columns (lowest column on ties); a wave per row picks the largest, again
-// the lowest column among equals, and records the token.
-__global__ __launch_bounds__(256) void k_gen_argmax(const int2* part, int32_t n_chunk, const int64_t* cnt,
-                                                    int64_t row0, const int64_t* gd, int32_t step, int32_t G,
-                                                    int32_t eos, int32_t pad, int32_t* tok, int32_t* done,
-                                                    int32_t* gen) {
-  const int64_t rows = *cnt, sb = gd[D_SEQ_BEGIN];
+// the lowest column among equals, records the token and, unless the row's
+// generation is over, writes the token's embedding for the next step (x, the
+// first norm's operand h = x * g, its row scale, the position): one launch where the
+// argmax and the embedding took 5 us each.
+__global__ __launch_bounds__(256) void k_gen_next(GenNextArgs a) {
+  const int64_t rows = *a.cnt, sb = a.gen_desc[D_SEQ_BEGIN];
+  const int n_chunk = a.vocab / 64;
+  const int ea = a.wdtype == AIQ_F16 ? ACT_F16 : ACT_BF16;
   const int lane = threadIdx.x & 63;
   const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
   for (int64_t r = wave; r < rows; r += n_waves) {
-    const int2* pr = part + r * n_chunk;
+    const int2* pr = static_cast<const int2*>(a.part) + r * n_chunk;
     float best = -INFINITY;
     int32_t bi = INT32_MAX;
     for (int c = lane; c < n_chunk; c += 64) {   // ascending columns: strict > keeps each lane's first maximum
@@ -490,23 +376,43 @@ __global__ __launch_bounds__(256) void k_gen_argmax(const int2* part, int32_t n_
       }
     }
     if (bi == INT32_MAX) bi = 0;   // no finite maximum (every logit NaN or -inf)
+    const int64_t i = a.row0 + r;
     if (lane == 0) {
-      const int64_t i = row0 + r;
-      const bool ended = done[i] != 0;
-      gen[(sb + i) * G + step] = ended ? pad : bi;
-      tok[i] = bi;
-      if (!ended && bi == eos) done[i] = 1;
+      const bool ended = a.done[i] != 0;
+      a.gen[(sb + i) * a.G + a.step] = ended ? a.pad : bi;
+      if (!ended && bi == a.eos) a.done[i] = 1;
     }
+    if (a.step + 1 == a.G) continue;
+    if (lane == 0) a.pos[i] = a.npre + static_cast<int32_t>(a.cu[sb + i + 1] - a.cu[sb + i]) + a.step;
+    const int d = a.d;
+    const uint16_t* er = static_cast<const uint16_t*>(a.emb) + static_cast<int64_t>(bi) * d;
+    float* xr = a.x + i * d;
+    uint16_t* hr = static_cast<uint16_t*>(a.h) + i * d;
+    float ssq = 0.f;
+    for (int c = lane * 4; c < d; c += 256) {
+      const uint2 v = *reinterpret_cast<const uint2*>(er + c);
+      float4 o;
+      o.x = act2f(static_cast<uint16_t>(v.x & 0xFFFFu), ea);
+      o.y = act2f(static_cast<uint16_t>(v.x >> 16), ea);
+      o.z = act2f(static_cast<uint16_t>(v.y & 0xFFFFu), ea);
+      o.w = act2f(static_cast<uint16_t>(v.y >> 16), ea);
+      *reinterpret_cast<float4*>(xr + c) = o;
+      const float4 gv = *reinterpret_cast<const float4*>(a.g + c);
+      uint2 hv;
+      hv.x = f2act(o.x * gv.x, a.h_act) | (static_cast<uint32_t>(f2act(o.y * gv.y, a.h_act)) << 16);
+      hv.y = f2act(o.z * gv.z, a.h_act) | (static_cast<uint32_t>(f2act(o.w * gv.w, a.h_act)) << 16);
+      *reinterpret_cast<uint2*>(hr + c) = hv;
+      ssq += (o.x * o.x + o.y * o.y) + (o.z * o.z + o.w * o.w);
+    }
+    ssq = wave_sum_g(ssq);
+    if (lane == 0) a.rs[i] = 1.0f / sqrtf(ssq / static_cast<float>(d) + a.eps);
   }
 }
 
-hipError_t launch_gen_argmax(const void* part, int32_t vocab, const int64_t* cnt, int64_t row0,
-                             const int64_t* gen_desc, int32_t step, int32_t G, int32_t eos, int32_t pad,
-                             int32_t* tok, int32_t* done, int32_t* gen, hipStream_t s) {
-  if (vocab % 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_gen_argmax, dim3(grid_for(GEN_HEAD_ROWS, 4, 1024)), dim3(256), 0, s,
-                     static_cast<const int2*>(part), vocab / 64, cnt, row0, gen_desc, step, G, eos, pad, tok, done,
-                     gen);
+hipError_t launch_gen_next(const GenNextArgs& a, hipStream_t s) {
+  if (a.vocab % 64 || (a.wdtype != AIQ_BF16 && a.wdtype != AIQ_F16) || a.h_act == ACT_F32 || a.d % 4)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_gen_next, dim3(grid_for(GEN_HEAD_ROWS, 4, 1024)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

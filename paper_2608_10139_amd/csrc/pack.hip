@@ -116,8 +116,15 @@ __device__ __forceinline__ int64_t lower_bound_cu(const int64_t* cu, int64_t n, 
   return lo;
 }
 
+__device__ __forceinline__ void write_rope_rev(const RopeRev& rr, int i) {
+  if (rr.rev && i < (rr.hd >> 1))
+    rr.rev[i] = static_cast<float>(pow(rr.theta, -2.0 * static_cast<double>(i) / static_cast<double>(rr.hd)) /
+                                   6.283185307179586);
+}
+
 __global__ void k_chunk_desc(const int64_t* cu, const int64_t* n_ptr, int64_t chunk_tokens, int64_t n_chunks,
-                             int64_t t_ub, int64_t* desc) {
+                             int64_t t_ub, int64_t* desc, RopeRev rr) {
+  if (blockIdx.x == 0) write_rope_rev(rr, threadIdx.x);
   // only sequences that end inside the packed buffer take part
   int64_t n = *n_ptr;
   {
@@ -141,9 +148,9 @@ __global__ void k_chunk_desc(const int64_t* cu, const int64_t* n_ptr, int64_t ch
 }
 
 hipError_t launch_chunk_desc(const int64_t* cu, const int64_t* n_ptr, int64_t chunk_tokens,
-                             int64_t n_chunks, int64_t t_ub, int64_t* desc, hipStream_t s) {
+                             int64_t n_chunks, int64_t t_ub, int64_t* desc, const RopeRev& rr, hipStream_t s) {
   hipLaunchKernelGGL(k_chunk_desc, dim3(grid_for(n_chunks, 256)), dim3(256), 0, s, cu, n_ptr,
-                     chunk_tokens, n_chunks, t_ub, desc);
+                     chunk_tokens, n_chunks, t_ub, desc, rr);
   return hipGetLastError();
 }
 
@@ -152,7 +159,9 @@ hipError_t launch_chunk_desc(const int64_t* cu, const int64_t* n_ptr, int64_t ch
 // least one token); a malformed array empties the chunk and sets a status bit
 // so no later kernel indexes outside the caller's buffers.
 __global__ __launch_bounds__(1024) void k_packed_desc(const int32_t* cu32, int32_t n_seq, int64_t n_tok,
-                                                      int64_t* cu64, int64_t* desc, int64_t* ctr) {
+                                                      int64_t* cu64, int64_t* desc, int64_t* ctr, RopeRev rr) {
+  if (threadIdx.x < C_COUNT) ctr[threadIdx.x] = 0;
+  write_rope_rev(rr, threadIdx.x);
   int bad = 0;
   for (int64_t i = threadIdx.x; i <= n_seq; i += blockDim.x) {
     const int64_t v = cu32[i];
@@ -168,13 +177,13 @@ __global__ __launch_bounds__(1024) void k_packed_desc(const int32_t* cu32, int32
     desc[D_SEQ_BEGIN] = 0;
     desc[D_NSEQ] = bad ? 0 : n_seq;
     ctr[C_NSEQ] = bad ? 0 : n_seq;
-    if (bad) ctr[C_STATUS] |= AIQ_DEV_LIST_LEN;
+    if (bad) ctr[C_STATUS] = AIQ_DEV_LIST_LEN;   // after the barrier that follows the clear
   }
 }
 
 hipError_t launch_packed_desc(const int32_t* cu32, int32_t n_seq, int64_t n_tok, int64_t* cu64,
-                              int64_t* desc, int64_t* ctr, hipStream_t s) {
-  hipLaunchKernelGGL(k_packed_desc, dim3(1), dim3(1024), 0, s, cu32, n_seq, n_tok, cu64, desc, ctr);
+                              int64_t* desc, int64_t* ctr, const RopeRev& rr, hipStream_t s) {
+  hipLaunchKernelGGL(k_packed_desc, dim3(1), dim3(1024), 0, s, cu32, n_seq, n_tok, cu64, desc, ctr, rr);
   return hipGetLastError();
 }
 
@@ -211,14 +220,8 @@ hipError_t launch_copy_row_f32(const float* src, float* dst, int32_t n, hipStrea
 
 // ------------------------------------------------------------------ rotary table
 // cos / sin of pos * theta**(-2i/hd), evaluated in fp64 and rounded to fp32.
-__global__ void k_rope_table(int32_t max_pos, int32_t half, double theta, int32_t hd, float* cos_t, float* sin_t,
-                             float* rev) {
+__global__ void k_rope_table(int32_t max_pos, int32_t half, double theta, int32_t hd, float* cos_t, float* sin_t) {
   const int64_t n = static_cast<int64_t>(max_pos) * half;
-  if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < half) {
-    const int i = threadIdx.x;
-    rev[i] = static_cast<float>(pow(theta, -2.0 * static_cast<double>(i) / static_cast<double>(hd)) /
-                                6.283185307179586);
-  }
   for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
     const int64_t p = j / half;
     const int i = static_cast<int>(j % half);
@@ -230,9 +233,9 @@ __global__ void k_rope_table(int32_t max_pos, int32_t half, double theta, int32_
 }
 
 hipError_t launch_rope_table(int32_t max_pos, int32_t half, double theta, int32_t hd, float* cos_t,
-                             float* sin_t, float* rev, hipStream_t s) {
+                             float* sin_t, hipStream_t s) {
   hipLaunchKernelGGL(k_rope_table, dim3(grid_for(static_cast<int64_t>(max_pos) * half, 256)), dim3(256), 0,
-                     s, max_pos, half, theta, hd, cos_t, sin_t, rev);
+                     s, max_pos, half, theta, hd, cos_t, sin_t);
   return hipGetLastError();
 }
 
@@ -263,8 +266,18 @@ template <bool NORM>
 __global__ __launch_bounds__(256) void k_embed(const int64_t* desc, const int64_t* cu, const int32_t* packed,
                                                const void* emb, int32_t wdtype, int32_t d, int32_t vocab,
                                                float* x, int32_t* pos, int64_t* ctr, const float* g, float eps,
-                                               void* h, int32_t h_act, float* rs, int32_t pos_base) {
+                                               void* h, int32_t h_act, float* rs, int32_t pos_base, LastDesc last) {
   const int64_t tb = desc[D_TOK_BEGIN], nt = desc[D_NTOK], sb = desc[D_SEQ_BEGIN], ns = desc[D_NSEQ];
+  if (NORM && blockIdx.x == 0)
+    for (int b = threadIdx.x; b < last.blocks; b += blockDim.x) {
+      int64_t r = ns - static_cast<int64_t>(b) * last.R;
+      r = r < 0 ? 0 : (r > last.R ? last.R : r);
+      int64_t* o = last.ldesc + static_cast<int64_t>(b) * D_STRIDE;
+      o[D_TOK_BEGIN] = tb;
+      o[D_NTOK] = r;
+      o[D_SEQ_BEGIN] = sb + static_cast<int64_t>(b) * last.R;
+      o[D_NSEQ] = r;
+    }
   const int lane = threadIdx.x & 63;
   const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -314,17 +327,17 @@ hipError_t launch_embed(const int64_t* desc, const int64_t* cu, const int32_t* p
                         const void* emb, int32_t wdtype, int32_t d, int32_t vocab, float* x, int32_t* pos,
                         int64_t* ctr, int64_t t_cap, hipStream_t s) {
   hipLaunchKernelGGL(k_embed<false>, dim3(grid_for(t_cap, 4, 8192)), dim3(256), 0, s, desc, cu, packed, emb,
-                     wdtype, d, vocab, x, pos, ctr, nullptr, 0.f, nullptr, 0, nullptr, 0);
+                     wdtype, d, vocab, x, pos, ctr, nullptr, 0.f, nullptr, 0, nullptr, 0, LastDesc{});
   return hipGetLastError();
 }
 
 hipError_t launch_embed_norm(const int64_t* desc, const int64_t* cu, const int32_t* packed, const void* emb,
                              int32_t wdtype, int32_t d, int32_t vocab, float* x, int32_t* pos, int64_t* ctr,
                              const float* g, float eps, void* h, int32_t h_act, float* rs, int64_t t_cap,
-                             hipStream_t s, int32_t pos_base) {
+                             hipStream_t s, int32_t pos_base, LastDesc last) {
   if (h_act == ACT_F32) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_embed<true>, dim3(grid_for(t_cap, 4, 8192)), dim3(256), 0, s, desc, cu, packed, emb,
-                     wdtype, d, vocab, x, pos, ctr, g, eps, h, h_act, rs, pos_base);
+                     wdtype, d, vocab, x, pos, ctr, g, eps, h, h_act, rs, pos_base, last);
   return hipGetLastError();
 }
 
