@@ -1078,7 +1078,11 @@ aiq_status aiq_run(const aiq_plan* p, void* ws, size_t ws_bytes, const aiq_out* 
   const void* pkey = p->has_build ? p->probe_cols[q.probe_key_col].data : nullptr;
   const int32_t pkey_dt = p->has_build ? p->probe_cols[q.probe_key_col].dtype : AIQ_I32;
 
-  HIP_TRY(launch_fill_i64(ctr, C_COUNT, 0, s));
+  int64_t* lb = at<int64_t>(ws, L.lb);
+  if (p->lb_compact)
+    HIP_TRY(launch_clear_select(ctr, lb, n, s));
+  else
+    HIP_TRY(launch_fill_i64(ctr, C_COUNT, 0, s));
   // ---- relational: WHERE (+ join) -> ascending survivor ids
   tr.begin(AIQ_K_REL);
   if (p->has_build) {
@@ -1097,9 +1101,9 @@ aiq_status aiq_run(const aiq_plan* p, void* ws, size_t ws_bytes, const aiq_out* 
   if (p->lb_compact) {
     // masks, compaction, join payloads and token offsets in one launch
     HIP_TRY(launch_select_lb(p->probe_preds, n, pkey, pkey_dt, h, p->has_build, p->has_build ? &staged : nullptr,
-                             ids1, cap1, ids2, cap2, payload,
-                             p->pairs ? nullptr : p->probe.list_offsets, p->probe.max_list_len, npre_rows, cu,
-                             at<int64_t>(ws, L.lb), ctr, s));
+                             ids1, cap1, ids2, cap2, p->rel_only ? nullptr : payload,
+                             p->pairs ? nullptr : p->probe.list_offsets, p->probe.max_list_len, npre_rows,
+                             p->rel_only ? nullptr : cu, lb, ctr, s));
   } else {
     HIP_TRY(launch_row_mask(p->probe_preds, n, pkey, pkey_dt, h, p->has_build, mask, blk_cnt, s));
     HIP_TRY(launch_scan_blocks(blk_cnt, nullptr, n, blk_off, ctr + C_SEL, s));
@@ -1151,8 +1155,12 @@ aiq_status aiq_run(const aiq_plan* p, void* ws, size_t ws_bytes, const aiq_out* 
     // relational part only: every selected id is kept
     tr.end();
     tr.begin(AIQ_K_AGG);
-    HIP_TRY(launch_keep_selected(ctr, out->ids_cap, s));
-    HIP_TRY(launch_finalize(ctr, out->scalars, s));
+    if (p->lb_compact) {
+      HIP_TRY(launch_finalize_rel(ctr, lb, n, out->ids_cap, out->scalars, s));
+    } else {
+      HIP_TRY(launch_keep_selected(ctr, out->ids_cap, s));
+      HIP_TRY(launch_finalize(ctr, out->scalars, s));
+    }
     tr.end();
     return AIQ_OK;
   }
@@ -1310,7 +1318,7 @@ aiq_status aiq_run_relational_static(const aiq_plan* p, const aiq_out* out, void
   StagedHash staged{at<int32_t>(base, o_jk), at<int32_t>(base, o_jv), at<int32_t>(base, o_jl)};
   const void* pkey = p->has_build ? p->probe_cols[q.probe_key_col].data : nullptr;
   const int32_t pkey_dt = p->has_build ? p->probe_cols[q.probe_key_col].dtype : AIQ_I32;
-  HIP_TRY(launch_fill_i64(ctr, C_COUNT, 0, s));
+  HIP_TRY(launch_clear_select(ctr, lb, p->n_rows, s));
   if (p->has_build) {
     HIP_TRY(launch_fill_i32(h.keys, static_cast<int64_t>(hcap), HASH_EMPTY, s));
     const aiq_col& kc = p->build_cols[q.build_key_col];
@@ -1322,8 +1330,7 @@ aiq_status aiq_run_relational_static(const aiq_plan* p, const aiq_out* out, void
   HIP_TRY(launch_select_lb(p->probe_preds, p->n_rows, pkey, pkey_dt, h, p->has_build,
                            p->has_build ? &staged : nullptr, out->ids, out->ids_cap, ids2, out->sel_cap, nullptr,
                            p->probe.list_offsets, p->probe.max_list_len, q.n_prefix, nullptr, lb, ctr, s));
-  HIP_TRY(launch_keep_selected(ctr, out->ids_cap, s));
-  HIP_TRY(launch_finalize(ctr, out->scalars, s));
+  HIP_TRY(launch_finalize_rel(ctr, lb, p->n_rows, out->ids_cap, out->scalars, s));
   return AIQ_OK;
 }
 

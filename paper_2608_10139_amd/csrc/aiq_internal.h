@@ -128,12 +128,12 @@ hipError_t launch_scatter_rows(const uint64_t* mask, const int64_t* blk_off, con
 hipError_t launch_cu_from_blocks(const int32_t* lens, const int64_t* blk_off, const int64_t* tok_off,
                                  int64_t n_ub, int64_t* cu, hipStream_t s);
 // WHERE (+ join), stable compaction and token offsets in one launch (decoupled
-// look-back over `lb`, 4 int64 per block of at least LB_MIN_ROWS rows,
-// cleared here first): out_ids
-// (and out_ids2) as launch_scatter_rows, ctr[C_SEL] = the count; with `off`
-// also ctr[C_TOK] = the total token count (per row min(list length,
-// max_len) + n_prefix) and, when cu is not NULL, cu[0..n_sel] (cu[i] =
-// tokens of the selected rows before i).
+// look-back over `lb`, 4 int64 per block of at least LB_MIN_ROWS rows, cleared
+// by launch_clear_select): out_ids (and out_ids2) as launch_scatter_rows,
+// ctr[C_SEL] = the count; with `off` and cu also ctr[C_TOK] = the total token
+// count (per row min(list length, max_len) + n_prefix) and cu[0..n_sel] (cu[i] =
+// tokens of the selected rows before i); with `off` alone the blocks' token
+// counts stay in lb for launch_finalize_rel.
 // A block's token sum must stay below 2^31: REL_ROWS_PER_BLOCK *
 // (max_len + n_prefix) < 2^31.
 // With a join and st non-null, the probes read the LDS-staged table (st,
@@ -143,6 +143,12 @@ hipError_t launch_select_lb(const DPredList& preds, int64_t n_rows, const void* 
                             int32_t* out_ids2, int64_t out_cap2, int32_t* out_payload, const int64_t* off,
                             int32_t max_len, int32_t n_prefix, int64_t* cu, int64_t* lb, int64_t* ctr,
                             hipStream_t s);
+// Clears ctr[0..C_COUNT) and the look-back words of n_rows rows.
+hipError_t launch_clear_select(int64_t* ctr, int64_t* lb, int64_t n_rows, hipStream_t s);
+// The scalars of a relational-only run after launch_select_lb without cu: every
+// selected row kept, flagged if above cap.
+hipError_t launch_finalize_rel(int64_t* ctr, const int64_t* lb, int64_t n_rows, int64_t cap, int64_t* scalars,
+                               hipStream_t s);
 // ctr[C_KEPT] = ctr[C_SEL] (every selected row kept), flagged if above cap.
 hipError_t launch_keep_selected(int64_t* ctr, int64_t cap, hipStream_t s);
 hipError_t launch_group_accumulate(const int32_t* sel, const int32_t* label, const int32_t* payload,

@@ -700,9 +700,81 @@ __device__ __forceinline__ int64_t wave_sum64(int64_t v) {
   return v;
 }
 
+// Wave 0 of block b (own totals cnt, tok already published): the totals of all
+// earlier blocks into sb[0..1], its inclusive ones published.  Lane l reads
+// block j - l.  When the nearest inclusive prefix is not in reach yet, the
+// leading run of published blocks is consumed and the walk continues behind it.
+template <bool CU>
+__device__ __forceinline__ void look_back(int64_t* lb, int64_t* ctr, int64_t b, int64_t cnt, int64_t tok,
+                                          int64_t* sb) {
+  const int lane = threadIdx.x & 63;
+  int64_t ec = 0, et = 0;
+  if (b > 0) {
+    int64_t j = b - 1;
+    int spins = 0;
+    for (;;) {
+      const int64_t idx = j - lane;
+      int state = 2;   // 2: inclusive prefix, 1: block totals only, 0: nothing yet
+      int64_t vc = 0, vt = 0;
+      if (idx >= 0) {   // idx < 0: the empty prefix before block 0
+        const int64_t* q = lb + 4 * idx;
+        const int64_t ag = lb_get(q), ic = lb_get(q + 1), it = CU ? lb_get(q + 2) : -1;
+        if (ic < 0 && it < 0) {
+          vc = ic & ~LB_SET;
+          if (CU) vt = it & ~LB_SET;
+        } else if (ag < 0) {
+          state = 1;
+          vc = CU ? ag & 0x3FFF : ag & ~LB_SET;
+          if (CU) vt = (ag >> 14) & 0x7FFFFFFF;
+        } else {
+          state = 0;
+        }
+      }
+      const uint64_t incl = __ballot(state == 2), ready = __ballot(state != 0);
+      const int p = incl ? __ffsll(static_cast<unsigned long long>(incl)) - 1 : 63;
+      const uint64_t need = p == 63 ? ~0ull : ((1ull << (p + 1)) - 1);
+      if ((ready & need) == need) {
+        ec += wave_sum64(lane <= p ? vc : 0);
+        if (CU) et += wave_sum64(lane <= p ? vt : 0);
+        if (incl) break;
+        j -= 64;
+      } else {
+        // lanes below the first unpublished one hold block totals only
+        const int q = __ffsll(static_cast<unsigned long long>(~ready)) - 1;
+        if (q > 0) {
+          ec += wave_sum64(lane < q ? vc : 0);
+          if (CU) et += wave_sum64(lane < q ? vt : 0);
+          j -= q;
+        } else if (++spins > LB_SPIN_LIMIT) {
+          if (lane == 0) set_status(ctr, AIQ_DEV_SCAN_WAIT);
+          break;
+        } else {
+          __builtin_amdgcn_s_sleep(1);
+        }
+      }
+    }
+    if (lane == 0) {
+      lb_put(lb + 4 * b + 1, ec + cnt);
+      if (CU) lb_put(lb + 4 * b + 2, et + tok);
+    }
+  }
+  if (lane == 0) {
+    sb[0] = ec;
+    sb[1] = et;
+  }
+}
+
 // STAGED (joins): the block first copies the rehashed build table into LDS
 // when it fits (st.log2_out > 0) and probes it there.
-template <bool STAGED>
+// CU: token offsets of every survivor are written (cu).  Without them (a
+// relational-only plan) positions need only the survivor counts: a block
+// publishes its count as soon as its masks are known and wave 0 walks back while
+// the others read the list lengths, whose sum goes to lb[4b + 3] for
+// k_finalize_rel.  With the offsets, whole relational call: 2^26 rows at 1 % 131 us,
+// 2^24 at 50 % 82, at 100 % 104; without: 124, 53, 59.  Blocks of 4,096 or 16,384
+// rows (143 and 159 us at 2^26), look-back steps of 128 or 256 predecessors (130, 144)
+// and fewer resident blocks (the same down to three per CU) are no better.
+template <bool STAGED, bool CU>
 __global__ __launch_bounds__(LB_THREADS) void k_select_lb(
     DPredList preds, int64_t n_rows, int64_t nb, const void* probe_key, int32_t pk_dt, HashArgs h, int join,
     StagedHash st, int32_t* out_ids, int64_t out_cap, int32_t* out_ids2, int64_t out_cap2, int32_t* out_payload,
@@ -726,7 +798,7 @@ __global__ __launch_bounds__(LB_THREADS) void k_select_lb(
   __shared__ int32_t wpre[LB_WORDS + 1];
   __shared__ int32_t wtot;
   __shared__ uint16_t rows[LB_ROWS];                      // block-relative row of each survivor, in order
-  __shared__ int32_t tx[LB_ROWS + LB_ROWS / 16];          // token counts, then their prefix
+  __shared__ int32_t tx[CU ? LB_ROWS + LB_ROWS / 16 : 1]; // token counts, then their prefix
   __shared__ int64_t red[LB_WAVES];
   __shared__ int32_t tscan[LB_WAVES];
   __shared__ int64_t sb[2];                               // count and tokens of all earlier blocks
@@ -768,6 +840,11 @@ __global__ __launch_bounds__(LB_THREADS) void k_select_lb(
   }
   __syncthreads();
   const int32_t cnt = wpre[LB_WORDS];
+  int64_t* me = lb + 4 * b;
+  if (!CU) {
+    if (t == 0) lb_put(b == 0 ? me + 1 : me, cnt);
+    if (w == 0) look_back<false>(lb, ctr, b, cnt, 0, sb);
+  }
   // token count of every survivor (list length from the low 32 bits of both
   // offsets, exact below 2^31), eight loads per thread in flight
   int64_t tok = 0;
@@ -796,7 +873,7 @@ __global__ __launch_bounds__(LB_THREADS) void k_select_lb(
           bad_len = true;
           len = len < 0 ? 0 : max_len;
         }
-        tx[lb_pad(i)] = len + n_prefix;
+        if (CU) tx[lb_pad(i)] = len + n_prefix;
         tok += len + n_prefix;
       }
     }
@@ -812,8 +889,7 @@ __global__ __launch_bounds__(LB_THREADS) void k_select_lb(
   }
   // publish this block's totals: block 0 has no predecessor, so its totals
   // are already its inclusive prefix
-  int64_t* me = lb + 4 * b;
-  if (t == 0) {
+  if (CU && t == 0) {
     if (b == 0) {
       lb_put(me + 1, cnt);
       lb_put(me + 2, tok);
@@ -824,7 +900,7 @@ __global__ __launch_bounds__(LB_THREADS) void k_select_lb(
   // exclusive prefix of the token counts inside the block: thread t owns
   // entries 16t .. 16t + 15, 32-bit sums (the plan bounds a block's tokens
   // below 2^31)
-  if (off) {
+  if (CU && off) {
     const int first = t * 16;
     const int lim = cnt - first < 16 ? cnt - first : 16;
     int32_t own = 0;
@@ -846,65 +922,7 @@ __global__ __launch_bounds__(LB_THREADS) void k_select_lb(
       run += v;
     }
   }
-  // look-back over the predecessors: lane l of wave 0 reads block j - l.
-  // When the nearest inclusive prefix is not in reach yet, the leading run of
-  // published blocks is consumed and the walk continues behind it.
-  if (w == 0) {
-    int64_t ec = 0, et = 0;
-    if (b > 0) {
-      int64_t j = b - 1;
-      int spins = 0;
-      for (;;) {
-        const int64_t idx = j - lane;
-        int state = 2;   // 2: inclusive prefix, 1: block totals only, 0: nothing yet
-        int64_t vc = 0, vt = 0;
-        if (idx >= 0) {   // idx < 0: the empty prefix before block 0
-          const int64_t* q = lb + 4 * idx;
-          const int64_t ag = lb_get(q), ic = lb_get(q + 1), it = lb_get(q + 2);
-          if (ic < 0 && it < 0) {
-            vc = ic & ~LB_SET;
-            vt = it & ~LB_SET;
-          } else if (ag < 0) {
-            state = 1;
-            vc = ag & 0x3FFF;
-            vt = (ag >> 14) & 0x7FFFFFFF;
-          } else {
-            state = 0;
-          }
-        }
-        const uint64_t incl = __ballot(state == 2), ready = __ballot(state != 0);
-        const int p = incl ? __ffsll(static_cast<unsigned long long>(incl)) - 1 : 63;
-        const uint64_t need = p == 63 ? ~0ull : ((1ull << (p + 1)) - 1);
-        if ((ready & need) == need) {
-          ec += wave_sum64(lane <= p ? vc : 0);
-          et += wave_sum64(lane <= p ? vt : 0);
-          if (incl) break;
-          j -= 64;
-        } else {
-          // lanes below the first unpublished one hold block totals only
-          const int q = __ffsll(static_cast<unsigned long long>(~ready)) - 1;
-          if (q > 0) {
-            ec += wave_sum64(lane < q ? vc : 0);
-            et += wave_sum64(lane < q ? vt : 0);
-            j -= q;
-          } else if (++spins > LB_SPIN_LIMIT) {
-            if (lane == 0) set_status(ctr, AIQ_DEV_SCAN_WAIT);
-            break;
-          } else {
-            __builtin_amdgcn_s_sleep(1);
-          }
-        }
-      }
-      if (lane == 0) {
-        lb_put(me + 1, ec + cnt);
-        lb_put(me + 2, et + tok);
-      }
-    }
-    if (lane == 0) {
-      sb[0] = ec;
-      sb[1] = et;
-    }
-  }
+  if (CU && w == 0) look_back<true>(lb, ctr, b, cnt, tok, sb);
   __syncthreads();
   const int64_t cb = sb[0], tb = sb[1];
   bool overflow = false;
@@ -917,7 +935,7 @@ __global__ __launch_bounds__(LB_THREADS) void k_select_lb(
       if (pos < out_cap2) out_ids2[pos] = id;
       else overflow = true;
     }
-    if (cu) cu[pos] = tb + tx[lb_pad(i)];
+    if (CU) cu[pos] = tb + tx[lb_pad(i)];
   }
   if (join && out_payload) {   // the build payload of each survivor's match
     for (int i = t; i < cnt; i += LB_THREADS) {
@@ -927,10 +945,13 @@ __global__ __launch_bounds__(LB_THREADS) void k_select_lb(
     }
   }
   if (overflow) set_status(ctr, AIQ_DEV_IDS_CAP);
+  if (!CU && t == 0) me[3] = tok;
   if (b == nb - 1 && t == 0) {
     ctr[C_SEL] = cb + cnt;
-    if (off) ctr[C_TOK] = tb + tok;
-    if (cu) cu[cb + cnt] = tb + tok;
+    if (CU) {
+      ctr[C_TOK] = tb + tok;
+      cu[cb + cnt] = tb + tok;
+    }
   }
 }
 
@@ -940,18 +961,34 @@ hipError_t launch_select_lb(const DPredList& preds, int64_t n_rows, const void* 
                             int32_t max_len, int32_t n_prefix, int64_t* cu, int64_t* lb, int64_t* ctr,
                             hipStream_t s) {
   const int64_t nb = (n_rows + LB_ROWS - 1) / LB_ROWS;
-  if (!off) cu = nullptr;   // no list column: no offsets to write (cu may also be NULL with one: totals only)
+  if (!off) cu = nullptr;   // no list column: no offsets to write
   if (nb == 0) return cu ? launch_fill_i64(cu, 1, 0, s) : hipSuccess;   // no rows: cu = {0}
-  hipError_t e = launch_fill_i64(lb, 4 * nb, 0, s);
-  if (e != hipSuccess) return e;
-  if (join && st)
-    hipLaunchKernelGGL(k_select_lb<true>, dim3(static_cast<unsigned>(nb)), dim3(LB_THREADS), 0, s, preds, n_rows,
-                       nb, probe_key, probe_key_dtype, h, join, *st, out_ids, out_cap, out_ids2, out_cap2,
-                       out_payload, off, max_len, n_prefix, cu, lb, ctr);
-  else
-    hipLaunchKernelGGL(k_select_lb<false>, dim3(static_cast<unsigned>(nb)), dim3(LB_THREADS), 0, s, preds, n_rows,
-                       nb, probe_key, probe_key_dtype, h, join, StagedHash{}, out_ids, out_cap, out_ids2, out_cap2,
-                       out_payload, off, max_len, n_prefix, cu, lb, ctr);
+  const StagedHash sh = join && st ? *st : StagedHash{};
+#define AIQ_SELECT(STAGED, CU)                                                                                    \
+  hipLaunchKernelGGL((k_select_lb<STAGED, CU>), dim3(static_cast<unsigned>(nb)), dim3(LB_THREADS), 0, s, preds,   \
+                     n_rows, nb, probe_key, probe_key_dtype, h, join, sh, out_ids, out_cap, out_ids2, out_cap2,   \
+                     out_payload, off, max_len, n_prefix, cu, lb, ctr)
+  if (join && st) {
+    if (cu) AIQ_SELECT(true, true);
+    else AIQ_SELECT(true, false);
+  } else {
+    if (cu) AIQ_SELECT(false, true);
+    else AIQ_SELECT(false, false);
+  }
+#undef AIQ_SELECT
+  return hipGetLastError();
+}
+
+// Clears the run's counters and the look-back words of n_rows rows.
+__global__ void k_clear_select(int64_t* ctr, int64_t* lb, int64_t n) {
+  if (blockIdx.x == 0 && threadIdx.x < C_COUNT) ctr[threadIdx.x] = 0;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    lb[i] = 0;
+}
+
+hipError_t launch_clear_select(int64_t* ctr, int64_t* lb, int64_t n_rows, hipStream_t s) {
+  const int64_t n = 4 * ((n_rows + LB_ROWS - 1) / LB_ROWS);
+  hipLaunchKernelGGL(k_clear_select, dim3(grid_for(n, 256)), dim3(256), 0, s, ctr, lb, n);
   return hipGetLastError();
 }
 
@@ -1130,6 +1167,39 @@ __global__ void k_finalize(const int64_t* ctr, int64_t* scalars, int32_t tok_per
 hipError_t launch_finalize(const int64_t* ctr, int64_t* scalars, hipStream_t s, int32_t tok_per_row,
                            int32_t seq_ctr) {
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(64), 0, s, ctr, scalars, tok_per_row, seq_ctr);
+  return hipGetLastError();
+}
+
+// The scalars of a relational-only run in one launch: every selected row is
+// kept, and the token total is the sum of the blocks' (lb[4b + 3]).
+__global__ __launch_bounds__(1024) void k_finalize_rel(int64_t* ctr, const int64_t* lb, int64_t nb, int64_t cap,
+                                                       int64_t* scalars) {
+  __shared__ int64_t part[16];
+  const int t = threadIdx.x;
+  int64_t tok = 0;
+  for (int64_t b = t; b < nb; b += 1024) tok += lb[4 * b + 3];
+  tok = wave_sum64(tok);
+  if ((t & 63) == 0) part[t >> 6] = tok;
+  __syncthreads();
+  if (t >= AIQ_N_SCALARS) return;
+  const int64_t n = ctr[C_SEL];
+  int64_t v = 0;
+  switch (t) {
+    case AIQ_S_SELECTED:
+    case AIQ_S_KEPT: v = n; break;
+    case AIQ_S_TOKENS:
+      for (int i = 0; i < 16; ++i) v += part[i];
+      break;
+    case AIQ_S_STATUS: v = ctr[C_STATUS] | (n > cap ? AIQ_DEV_IDS_CAP : 0); break;
+    default: break;
+  }
+  scalars[t] = v;
+}
+
+hipError_t launch_finalize_rel(int64_t* ctr, const int64_t* lb, int64_t n_rows, int64_t cap, int64_t* scalars,
+                               hipStream_t s) {
+  hipLaunchKernelGGL(k_finalize_rel, dim3(1), dim3(1024), 0, s, ctr, lb, (n_rows + LB_ROWS - 1) / LB_ROWS, cap,
+                     scalars);
   return hipGetLastError();
 }
 
