@@ -243,9 +243,6 @@ hipError_t launch_rope_table(int32_t max_pos, int32_t half, double theta, int32_
 // One wave per chunk token (grid-stride): x[t, :] = E[tok, :] in fp32 and
 // pos[t] = position of the token inside its own sequence, found by a 64-way
 // search of the chunk's sequence offsets (each round narrows the range 64x).
-// With a norm gain `g` (MFMA path) the wave also writes h[t, :] = x * g in 16
-// bits and rs[t] = 1 / sqrt(mean(x^2) + eps): the first RMSNorm, applied by
-// the first projection.
 __device__ __forceinline__ int64_t seq_of(const int64_t* cu, int64_t sb, int64_t ns, int64_t gt, int lane) {
   int64_t lo = sb, n = ns;   // answer in [lo, lo + n): the last i with cu[i] <= gt
   while (n > 1) {
@@ -262,13 +259,42 @@ __device__ __forceinline__ int64_t seq_of(const int64_t* cu, int64_t sb, int64_t
   return lo;
 }
 
-template <bool NORM>
 __global__ __launch_bounds__(256) void k_embed(const int64_t* desc, const int64_t* cu, const int32_t* packed,
-                                               const void* emb, int32_t wdtype, int32_t d, int32_t vocab,
-                                               float* x, int32_t* pos, int64_t* ctr, const float* g, float eps,
-                                               void* h, int32_t h_act, float* rs, int32_t pos_base, LastDesc last) {
+                                               const float* emb, int32_t d, int32_t vocab, float* x, int32_t* pos,
+                                               int64_t* ctr) {
   const int64_t tb = desc[D_TOK_BEGIN], nt = desc[D_NTOK], sb = desc[D_SEQ_BEGIN], ns = desc[D_NSEQ];
-  if (NORM && blockIdx.x == 0)
+  const int lane = threadIdx.x & 63;
+  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
+  const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  for (int64_t t = wave; t < nt; t += n_waves) {
+    const int64_t gt = tb + t;
+    int32_t tok = packed[gt];
+    if (tok < 0 || tok >= vocab) {   // only reachable through caller-packed batches
+      if (lane == 0) set_status(ctr, AIQ_DEV_TOKEN_RANGE);
+      tok = 0;
+    }
+    const int64_t sq = seq_of(cu, sb, ns, gt, lane);
+    if (lane == 0) pos[t] = static_cast<int32_t>(gt - cu[sq]);
+    for (int c = lane * 4; c < d; c += 256)
+      *reinterpret_cast<float4*>(x + t * d + c) =
+          *reinterpret_cast<const float4*>(emb + static_cast<int64_t>(tok) * d + c);
+  }
+}
+
+// The MFMA path's form: a wave takes EMB_RUN consecutive tokens (one search for
+// the first one's sequence), their rows' 16-byte pieces in flight together, and
+// also writes h = x * g in 16 bits and rs = 1 / sqrt(mean(x^2) + eps).  Bound: the h rows
+// written (466,000 rows of d 512: 172 us; token by token with 8-byte pieces 260).
+constexpr int EMB_RUN = 4;
+
+template <bool F16>
+__global__ __launch_bounds__(256) void k_embed_norm(const int64_t* desc, const int64_t* cu, const int32_t* packed,
+                                                    const uint16_t* emb, int32_t d, int32_t vocab, float* x,
+                                                    int32_t* pos, int64_t* ctr, const float* g, float eps, uint16_t* h,
+                                                    float* rs, int32_t pos_base, LastDesc last) {
+  constexpr int act = F16 ? ACT_F16 : ACT_BF16;
+  const int64_t tb = desc[D_TOK_BEGIN], nt = desc[D_NTOK], sb = desc[D_SEQ_BEGIN], ns = desc[D_NSEQ];
+  if (blockIdx.x == 0)
     for (int b = threadIdx.x; b < last.blocks; b += blockDim.x) {
       int64_t r = ns - static_cast<int64_t>(b) * last.R;
       r = r < 0 ? 0 : (r > last.R ? last.R : r);
@@ -281,44 +307,65 @@ __global__ __launch_bounds__(256) void k_embed(const int64_t* desc, const int64_
   const int lane = threadIdx.x & 63;
   const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t t = wave; t < nt; t += n_waves) {
-    const int64_t gt = tb + t;
-    int32_t tok = packed[gt];
-    if (tok < 0 || tok >= vocab) {   // only reachable through caller-packed batches
-      if (lane == 0) set_status(ctr, AIQ_DEV_TOKEN_RANGE);
-      tok = 0;
-    }
-    const int64_t sq = seq_of(cu, sb, ns, gt, lane);
-    if (lane == 0) pos[t] = pos_base + static_cast<int32_t>(gt - cu[sq]);
-    float* xr = x ? x + t * d : nullptr;   // null: x is not written (the first projection reads the table)
-    float ssq = 0.f;
-    for (int c = lane * 4; c < d; c += 256) {
-      float4 o;
-      if (wdtype == AIQ_BF16 || wdtype == AIQ_F16) {
-        const int ea = wdtype == AIQ_F16 ? ACT_F16 : ACT_BF16;
-        const uint16_t* er = static_cast<const uint16_t*>(emb) + static_cast<int64_t>(tok) * d;
-        const uint2 v = *reinterpret_cast<const uint2*>(er + c);
-        o.x = act2f(static_cast<uint16_t>(v.x & 0xFFFFu), ea);
-        o.y = act2f(static_cast<uint16_t>(v.x >> 16), ea);
-        o.z = act2f(static_cast<uint16_t>(v.y & 0xFFFFu), ea);
-        o.w = act2f(static_cast<uint16_t>(v.y >> 16), ea);
-      } else {
-        o = *reinterpret_cast<const float4*>(static_cast<const float*>(emb) + static_cast<int64_t>(tok) * d + c);
-      }
-      if (x) *reinterpret_cast<float4*>(xr + c) = o;
-      if (NORM) {
-        const float4 gv = *reinterpret_cast<const float4*>(g + c);
-        uint2 hv;
-        hv.x = f2act(o.x * gv.x, h_act) | (static_cast<uint32_t>(f2act(o.y * gv.y, h_act)) << 16);
-        hv.y = f2act(o.z * gv.z, h_act) | (static_cast<uint32_t>(f2act(o.w * gv.w, h_act)) << 16);
-        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(h) + t * d + c) = hv;
-        ssq += (o.x * o.x + o.y * o.y) + (o.z * o.z + o.w * o.w);
+  for (int64_t t0 = wave * EMB_RUN; t0 < nt; t0 += n_waves * EMB_RUN) {
+    const int n = nt - t0 < EMB_RUN ? static_cast<int>(nt - t0) : EMB_RUN;
+    // lane u < n: token t0 + u and its position
+    int32_t tok = 0;
+    if (lane < n) {
+      tok = packed[tb + t0 + lane];
+      if (tok < 0 || tok >= vocab) {   // only reachable through caller-packed batches
+        set_status(ctr, AIQ_DEV_TOKEN_RANGE);
+        tok = 0;
       }
     }
-    if (NORM) {
+    int64_t sq = seq_of(cu, sb, ns, tb + t0, lane);
+    if (lane < n) {
+      const int64_t gt = tb + t0 + lane;
+      while (sq + 1 < sb + ns && cu[sq + 1] <= gt) ++sq;   // at most EMB_RUN - 1 tokens on (empty lists skipped)
+      pos[t0 + lane] = pos_base + static_cast<int32_t>(gt - cu[sq]);
+    }
+    const uint16_t* er[EMB_RUN];
+    float ssq[EMB_RUN];
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) ssq += __shfl_xor(ssq, o);
-      if (lane == 0) rs[t] = 1.0f / sqrtf(ssq / static_cast<float>(d) + eps);
+    for (int u = 0; u < EMB_RUN; ++u) {
+      er[u] = emb + static_cast<int64_t>(__builtin_amdgcn_readlane(tok, u)) * d;
+      ssq[u] = 0.f;
+    }
+    for (int c = lane * 8; c < d; c += 512) {
+      uint4 v[EMB_RUN];
+#pragma unroll
+      for (int u = 0; u < EMB_RUN; ++u) v[u] = *reinterpret_cast<const uint4*>(er[u] + c);   // rows past n: token 0's
+      const float4 g0 = *reinterpret_cast<const float4*>(g + c), g1 = *reinterpret_cast<const float4*>(g + c + 4);
+      const float gv[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+#pragma unroll
+      for (int u = 0; u < EMB_RUN; ++u) {
+        if (u >= n) break;
+        const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+        float o[8];
+        uint32_t hw[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          o[2 * e] = act2f(static_cast<uint16_t>(w[e] & 0xFFFFu), act);
+          o[2 * e + 1] = act2f(static_cast<uint16_t>(w[e] >> 16), act);
+          hw[e] = f2act(o[2 * e] * gv[2 * e], act) |
+                  (static_cast<uint32_t>(f2act(o[2 * e + 1] * gv[2 * e + 1], act)) << 16);
+        }
+        const int64_t at = (t0 + u) * d + c;
+        *reinterpret_cast<uint4*>(h + at) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+        if (x) {   // null: x is not written (the first projection reads the table)
+          *reinterpret_cast<float4*>(x + at) = make_float4(o[0], o[1], o[2], o[3]);
+          *reinterpret_cast<float4*>(x + at + 4) = make_float4(o[4], o[5], o[6], o[7]);
+        }
+        ssq[u] += ((o[0] * o[0] + o[1] * o[1]) + (o[2] * o[2] + o[3] * o[3])) +
+                  ((o[4] * o[4] + o[5] * o[5]) + (o[6] * o[6] + o[7] * o[7]));
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < EMB_RUN; ++u) {
+      float s = ssq[u];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+      if (lane == u && u < n) rs[t0 + u] = 1.0f / sqrtf(s / static_cast<float>(d) + eps);
     }
   }
 }
@@ -326,8 +373,9 @@ __global__ __launch_bounds__(256) void k_embed(const int64_t* desc, const int64_
 hipError_t launch_embed(const int64_t* desc, const int64_t* cu, const int32_t* packed,
                         const void* emb, int32_t wdtype, int32_t d, int32_t vocab, float* x, int32_t* pos,
                         int64_t* ctr, int64_t t_cap, hipStream_t s) {
-  hipLaunchKernelGGL(k_embed<false>, dim3(grid_for(t_cap, 4, 8192)), dim3(256), 0, s, desc, cu, packed, emb,
-                     wdtype, d, vocab, x, pos, ctr, nullptr, 0.f, nullptr, 0, nullptr, 0, LastDesc{});
+  if (wdtype != AIQ_F32) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_embed, dim3(grid_for(t_cap, 4, 8192)), dim3(256), 0, s, desc, cu, packed,
+                     static_cast<const float*>(emb), d, vocab, x, pos, ctr);
   return hipGetLastError();
 }
 
@@ -335,9 +383,15 @@ hipError_t launch_embed_norm(const int64_t* desc, const int64_t* cu, const int32
                              int32_t wdtype, int32_t d, int32_t vocab, float* x, int32_t* pos, int64_t* ctr,
                              const float* g, float eps, void* h, int32_t h_act, float* rs, int64_t t_cap,
                              hipStream_t s, int32_t pos_base, LastDesc last) {
-  if (h_act == ACT_F32) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_embed<true>, dim3(grid_for(t_cap, 4, 8192)), dim3(256), 0, s, desc, cu, packed, emb,
-                     wdtype, d, vocab, x, pos, ctr, g, eps, h, h_act, rs, pos_base, last);
+  if (d % 8 || h_act != (wdtype == AIQ_F16 ? ACT_F16 : ACT_BF16) || (wdtype != AIQ_F16 && wdtype != AIQ_BF16))
+    return hipErrorInvalidValue;
+  const dim3 grid(grid_for(t_cap, 4 * EMB_RUN, 8192));
+  if (wdtype == AIQ_F16)
+    hipLaunchKernelGGL(k_embed_norm<true>, grid, dim3(256), 0, s, desc, cu, packed, static_cast<const uint16_t*>(emb), d,
+                       vocab, x, pos, ctr, g, eps, static_cast<uint16_t*>(h), rs, pos_base, last);
+  else
+    hipLaunchKernelGGL(k_embed_norm<false>, grid, dim3(256), 0, s, desc, cu, packed, static_cast<const uint16_t*>(emb), d,
+                       vocab, x, pos, ctr, g, eps, static_cast<uint16_t*>(h), rs, pos_base, last);
   return hipGetLastError();
 }
 
