@@ -15,7 +15,8 @@
 // M (tokens in the chunk) is read from device memory; the grid is persistent
 // (one workgroup per CU) and walks the tiles, so an empty chunk costs one
 // launch and no work.  Where M leaves 256 x 256 tiles too few for the chip the
-// same launch takes 128 x 128 or 64 x 64 ones (tile_path).
+// same launch takes 128 x 128 or 64 x 64 ones, also for the rows that would fill the
+// last round of large tiles in part (tile_plan).
 //
 // fp32 path: 32 x 64 tiles on the fp32 matrix instructions with the same row
 // mapping, used for fp32 models.
@@ -547,7 +548,7 @@ template <int BN>
 __device__ __forceinline__ int tslot(int r, int c) { return r * (BN / 4) + (c ^ (r & 15)); }
 
 template <int EPI, bool H, int BM, int BN, int SLABS>
-__device__ __forceinline__ void gemm_tiles(const GemmArgs& a, int64_t M, uint16_t* st0, uint16_t* st1, uint16_t* st2,
+__device__ __forceinline__ void gemm_tiles(const GemmArgs& a, int64_t mb, int64_t M, uint16_t* st0, uint16_t* st1, uint16_t* st2,
                                            uint16_t* st3, float* rbuf, int32_t* pbuf, const float* rvbuf) {
   static_assert(SLABS * (BM + BN) * GK * 2 == ST_BYTES, "stage size");
   typedef typename Op16<H>::V V;
@@ -561,7 +562,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, int64_t M, uint16_
   const int l32 = lane & 31, hi = lane >> 5, lr = lane >> 3;
   static_assert(BM == BN, "each wave copies as many pieces of A as of W");
   const int tiles_n = a.N / BN;
-  const int tiles_m = static_cast<int>((M + BM - 1) / BM);
+  const int tiles_m = static_cast<int>((M - mb + BM - 1) / BM);   // rows mb .. M - 1
   const int tiles = tiles_m * tiles_n;
   const int ns = a.K / (GK * SLABS);
   // XCD x takes a contiguous eighth of the tiles in column-major order: equal
@@ -573,7 +574,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, int64_t M, uint16_
 
   for (int tile = lo + static_cast<int>(blockIdx.x >> 3); tile < end; tile += per_xcd) {
     const int col = tile / tiles_m;
-    const int64_t m0 = static_cast<int64_t>(tile - col * tiles_m) * BM;
+    const int64_t m0 = mb + static_cast<int64_t>(tile - col * tiles_m) * BM;
     const int n0 = col * BN;
     const int rows = M - m0 < BM ? static_cast<int>(M - m0) : BM;
     __syncthreads();   // the previous tile's epilogue is done with the stages, rbuf and pbuf
@@ -741,29 +742,54 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& a, int64_t M, uint16_
   }
 }
 
-// Which tiles a launch of M rows takes: the shape whose rounds over the grid
-// cost least.  Costs in microseconds of one round, per 64-deep k-step and for
+// Which tiles a launch of M rows takes: 256 x 256 ones for the rows before the
+// returned one, 128 x 128 or 64 x 64 (`t64`) for the others, by the rounds over
+// the grid.  Costs in microseconds of one round, per 64-deep k-step and for
 // start plus epilogue, fitted to single rounds at K = 512 .. 8192 with cold
 // weights: 64 x 64 tiles 0.21 / 2.2 (10 us at K = 2048, 30 at 8192), 128 x 128
 // 0.53 / 4.5 (21, 69), 256 x 256 1.44 / 11 (60, 196; the maxima epilogue
-// takes 40).  The 256-row tiles' rounds count by XCD, whose rows they are
-// dealt to in turn.  They also need a whole tile of rows (tile_sources) and row
+// takes 15).  The 256-row tiles' rounds count by XCD, whose rows they are
+// dealt to in turn.  They also need a whole tile of rows (the sources of rows past M) and row
 // scales, not sums (`large`).
 // Measured at K = 3072, N = 3072: M = 120 17 us against 92 with the large
 // tiles only, M = 800 37 against 91, M = 1920 70 against 91, M = 3300 112
-// against 93.
-enum TilePath : int { PATH_256 = 0, PATH_128 = 1, PATH_64 = 2 };
+// against 93.  Where the last round of large tiles would be partly empty, the rows
+// past the last whole one go to small tiles: N = 2048, K = 8192, M = 18,200 (2.25 rounds)
+// 608 us against 670, N = 512, K = 2048, M = 66,000 195 against 236.
 template <int EPI>
-__device__ __forceinline__ int tile_path(int64_t M, int N, int K, int wgs, bool large) {
-  auto rounds = [](int64_t tiles, int slots) { return static_cast<float>((tiles + slots - 1) / slots); };
-  auto tiles = [&](int b) { return ((M + b - 1) / b) * (N / b); };
+__device__ __forceinline__ int64_t tile_plan(int64_t M, int N, int K, int wgs, bool large, bool& t64) {
+  auto rounds = [](int64_t tiles, int slots) {
+    return static_cast<float>(static_cast<uint32_t>(tiles + slots - 1) / static_cast<uint32_t>(slots));
+  };
   const float k = static_cast<float>(K / GK);
-  const float c64 = rounds(tiles(64), wgs) * (0.21f * k + 2.2f);
-  const float c128 = rounds(tiles(128), wgs) * (0.53f * k + 4.5f);
-  const int64_t rows_x = ((M + GM - 1) / GM + 7) / 8;
-  const float c256 = rounds(rows_x * (N / GN), wgs >> 3) * (1.44f * k + (EPI == EPI_ARGMAX ? 40.f : 11.f));
-  if (large && M >= GM && c256 <= c128 && c256 <= c64) return PATH_256;
-  return c128 < c64 ? PATH_128 : PATH_64;
+  const int tn64 = N / 64, tn128 = N / 128, tn = N / GN, per = wgs >> 3;
+  auto c64 = [&](int64_t m) { return rounds((m + 63) / 64 * tn64, wgs) * (0.21f * k + 2.2f); };
+  auto c128 = [&](int64_t m) { return rounds((m + 127) / 128 * tn128, wgs) * (0.53f * k + 4.5f); };
+  const float e256 = 1.44f * k + (EPI == EPI_ARGMAX ? 15.f : 11.f);
+  int64_t m1 = 0;
+  if (large && M >= GM) {
+    m1 = M;
+    float best = rounds(((M + GM - 1) / GM + 7) / 8 * tn, per) * e256;
+    if (M < 65536) {   // all rows small only pays where there are few rounds
+      const float all = fminf(c64(M), c128(M));
+      if (all < best) {
+        best = all;
+        m1 = 0;
+      }
+    }
+    const int64_t rx = M / (8 * GM);   // whole tile rows per XCD
+#pragma unroll 1
+    for (int64_t r = rx; r > 0 && r > rx - 8; --r) {
+      const int64_t rest = M - r * (8 * GM);
+      const float c = rounds(r * tn, per) * e256 + (rest ? fminf(c64(rest), c128(rest)) : 0.f);
+      if (c < 0.97f * best) {
+        best = c;
+        m1 = r * (8 * GM);
+      }
+    }
+  }
+  t64 = c64(M - m1) <= c128(M - m1);
+  return m1;
 }
 
 template <int EPI, bool H>
@@ -783,9 +809,8 @@ __global__ __launch_bounds__(GT, 1) void k_gemm_bf16(GemmArgs a) {
   const int64_t tok0 = EPI == EPI_RESID_EMB ? a.x_tok_desc[D_TOK_BEGIN] : 0;   // the rows' first packed token
   if (EPI == EPI_QKV_ROPE && static_cast<int>(threadIdx.x) < (a.hd >> 1))
     rvbuf[threadIdx.x] = a.rope_rev[threadIdx.x];   // visible after the first barrier
-  const int path = tile_path<EPI>(M, a.N, a.K, gridDim.x, !a.ssp_in);
-  if (path == PATH_64) return gemm_tiles<EPI, H, 64, 64, 2>(a, M, sA0, sB0, sA1, sB1, rbuf, pbuf, rvbuf);
-  if (path == PATH_128) return gemm_tiles<EPI, H, 128, 128, 1>(a, M, sA0, sB0, sA1, sB1, rbuf, pbuf, rvbuf);
+  bool t64;
+  const int64_t M1 = tile_plan<EPI>(M, a.N, a.K, gridDim.x, !a.ssp_in, t64);   // rows of 256-row tiles
   const int tiles_n = a.N / GN;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, wm = w >> 1, wn = w & 1;
   const int nk = a.K / GK;   // even (the launcher checks K % 128)
@@ -800,7 +825,7 @@ __global__ __launch_bounds__(GT, 1) void k_gemm_bf16(GemmArgs a) {
   // rows (gate/up 1-1.8 %, O 1-3.6 %, down 0.6-1.8 % faster than 4), 4 for
   // the q|k|v projection (2 is 2-3 % slower there).
   constexpr int group_m = EPI == EPI_QKV_ROPE ? 4 : 2;
-  const int tiles_m = static_cast<int>((M + GM - 1) / GM);   // < 2^31 (M < 2^39)
+  const int tiles_m = static_cast<int>((M1 + GM - 1) / GM);   // < 2^31 (M < 2^39)
   const int xcd = blockIdx.x & 7;
   const int per_xcd = gridDim.x >> 3;   // grid is a multiple of 8
   const int rows_x = tiles_m > xcd ? (tiles_m - xcd + 7) / 8 : 0;
@@ -822,14 +847,15 @@ __global__ __launch_bounds__(GT, 1) void k_gemm_bf16(GemmArgs a) {
     n0 = static_cast<int>(col) * GN;
   };
   int q = blockIdx.x >> 3;
-  if (q >= count_x) return;
   const uint16_t* ga[8];
   const uint16_t* gb[8];
-  int64_t m0;
-  int n0;
-  tile_mn(q, m0, n0);
-  tile_sources<EPI>(a, A, M, m0, n0, w, lane, ga, gb);
-  dma_stage(sA0, sB0, ga, gb, w);
+  int64_t m0 = 0;
+  int n0 = 0;
+  if (q < count_x) {
+    tile_mn(q, m0, n0);
+    tile_sources<EPI>(a, A, M, m0, n0, w, lane, ga, gb);
+    dma_stage(sA0, sB0, ga, gb, w);
+  }
   for (; q < count_x; q += per_xcd) {
     f32x16 acc[4][4];
 #pragma unroll
@@ -880,6 +906,11 @@ __global__ __launch_bounds__(GT, 1) void k_gemm_bf16(GemmArgs a) {
   // the last tile's re-read of its last k-block lands before the workgroup
   // gives up its LDS
   __builtin_amdgcn_s_waitcnt(0);
+  if (M1 >= M) return;
+  if (t64)
+    gemm_tiles<EPI, H, 64, 64, 2>(a, M1, M, sA0, sB0, sA1, sB1, rbuf, pbuf, rvbuf);
+  else
+    gemm_tiles<EPI, H, 128, 128, 1>(a, M1, M, sA0, sB0, sA1, sB1, rbuf, pbuf, rvbuf);
 }
 
 hipError_t launch_gemm_bf16(int epi, const GemmArgs& a, hipStream_t s) {

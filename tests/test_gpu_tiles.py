@@ -1,5 +1,6 @@
-"""The projection GEMM takes 64 x 64, 128 x 128 or 256 x 256 tiles by the number
-of rows M of a launch.  A row's result must not depend on which of them ran
+"""The projection GEMM takes 64 x 64, 128 x 128 or 256 x 256 tiles (or 256-row ones
+and smaller ones for the last rows) by the number of rows M of a launch, and
+small batches share an attention item's query blocks out.  A row's result must not depend on which of them ran
 (each output is one accumulator over K in order): the same sequence alone, in
 batches at the edges of the tiles and inside a batch large enough for the
 256-row tiles gives the same bits, full-vocabulary head included, and agrees
@@ -24,7 +25,7 @@ MODELS = {
 }
 LARGE = 40000   # tokens: 256-row tiles for every projection of both models
 # one sequence per length; the batches' totals sit at tile edges
-TOTALS = (1, 31, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513, 1023, 2049)
+TOTALS = (1, 31, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513, 1023, 1024, 1025, 2049, 8300, 18200)
 _M = {}
 
 
@@ -55,7 +56,7 @@ def test_row_bits_do_not_depend_on_tiles(name, compute, full_vocab):
     def seq(n):
         return r.integers(3, 1024, n).astype(np.int32)
 
-    probe = [seq(1), seq(64), seq(100), seq(255)]
+    probe = [seq(1), seq(64), seq(100), seq(255), seq(700)]
     # the probes at the head of a batch large enough for 256-row tiles
     filler = [seq(int(n)) for n in r.integers(16, 400, LARGE // 208)]
     print("large batch", flush=True)
@@ -66,13 +67,13 @@ def test_row_bits_do_not_depend_on_tiles(name, compute, full_vocab):
             rest = total - len(p)
             if rest < 0:
                 continue
-            seqs = [p] + ([seq(rest)] if rest else [])
+            seqs = [p] + [seq(min(1000, rest - o)) for o in range(0, rest, 1000)]
             got = prefill(dm, seqs, full_vocab)[0]
             assert np.array_equal(got, want[i]), (total, i)
     # many sequences: the last layer's rows and the head at M = sequences
     for n in (63, 64, 65, 129, 300):
         print("sequences", n, flush=True)
-        got = prefill(dm, [seq(9) for _ in range(n - 4)] + probe, full_vocab)[-4:]
+        got = prefill(dm, [seq(9) for _ in range(n - len(probe))] + probe, full_vocab)[-len(probe):]
         assert np.array_equal(got, want), n
     if not full_vocab and compute == "f16":
         assert np.abs(want - oracle.label_logits(m, probe, (1, 2))).max() <= TOL_BF16
