@@ -406,7 +406,7 @@ aiq_status aiq_workspace_size(const aiq_plan* plan, size_t* bytes);
  * bound fixed at plan creation from the table's token total (chunks that
  * the selection leaves empty cost one launch per kernel and no work), plus
  * one pass for a shared prompt prefix.  Each pass launches the embedding,
- * per layer the four projections, attention and the norm row scales, and,
+ * per layer the four projections, attention and (over 1,024 rows) the norm row scales, and,
  * except the prefix pass, the label head.  For sizing trace buffers
  * (aiq_trace).  Errors: AIQ_EINVAL (NULL argument, prefill-only plan).
  */
