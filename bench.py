@@ -335,8 +335,9 @@ def relational_scale_leg(B, torch, sizes, thresholds, steps: int = 5, multipass:
     Algorithmic bytes per run: 4 B of c per row, 4 B per selected id written,
     8 B per distinct offset entry read (off[r] and off[r + 1] of every
     selected row r: 16 B per row when the selected rows are isolated, 8 B
-    when they are adjacent), 8 B per cu_seqlens entry written.  The counts
-    are checked against numpy on the host."""
+    when they are adjacent) and, in the multi-launch form, 8 B per
+    cu_seqlens entry written (the one-launch form of a relational-only plan
+    writes none).  The counts are checked against numpy on the host."""
     import dataclasses
     from paper_2608_10139_amd.device import DeviceModel, DeviceQuery
     from synth import WORKLOADS
@@ -377,7 +378,7 @@ def relational_scale_leg(B, torch, sizes, thresholds, steps: int = 5, multipass:
             rel = float(np.sum(kinds.get(B.AIQ_K_REL, []))) / steps
             pack = float(np.sum(kinds.get(B.AIQ_K_PACK, []))) / steps
             agg = float(np.sum(kinds.get(B.AIQ_K_AGG, []))) / steps
-            nbytes = 4 * n + 4 * n_sel + 8 * n_off + 8 * (n_sel + 1)
+            nbytes = 4 * n + 4 * n_sel + 8 * n_off + (8 * (n_sel + 1) if multipass else 0)
             gbps = nbytes / ((rel + pack) * 1e-3) / 1e9
             out.append({"rows": n, "predicate": f"c < {k}", "selected": n_sel, "tokens": res["n_tokens"],
                         "where_compact_ms": round(rel, 4), "token_counts_ms": round(pack, 4),
