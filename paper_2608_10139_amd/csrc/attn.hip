@@ -419,15 +419,18 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
           s[j] = key <= qi && key < L ? dot * scale : -INFINITY;
           mx = fmaxf(mx, s[j]);
         }
-        if (mx == -INFINITY) continue;   // none of this lane's keys precede the query
+        // none of this lane's keys precede the query: told by position, since
+        // fmaxf drops NaN and a NaN score has to reach l and o
+        if (kb * 64 + part > qi) continue;
         const float m_new = fmaxf(m, mx);
-        const float alpha = expf(m - m_new);
+        const float ref = m_new == -INFINITY ? 0.f : m_new;   // no finite score yet: weights are 0 or NaN
+        const float alpha = expf(m - ref);
         l *= alpha;
 #pragma unroll
         for (int i = 0; i < HD / 4; ++i) o[i] *= alpha;
 #pragma unroll
         for (int j = 0; j < KT; ++j) {
-          const float pr = expf(s[j] - m_new);   // 0 for keys after the query
+          const float pr = expf(s[j] - ref);   // 0 for keys after the query
           l += pr;
 #pragma unroll
           for (int i = 0; i < HD / 4; ++i) {
@@ -438,7 +441,7 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
         }
         m = m_new;
       }
-      // merge the four partial states (the query's own key makes one finite)
+      // merge the four partial states; 0 * NaN keeps a NaN of a lane without a finite score
       float mm = fmaxf(m, __shfl_xor(m, 1));
       mm = fmaxf(mm, __shfl_xor(mm, 2));
       const float wgt = m == -INFINITY ? 0.f : expf(m - mm);
