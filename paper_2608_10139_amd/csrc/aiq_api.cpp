@@ -721,13 +721,12 @@ aiq_status enqueue_generation(const aiq_plan* p, void* ws, const Layout& L, cons
   };
   const bool fold = su <= RS_FOLD_ROWS;   // row scales taken where they are used
   const float* g0 = p->n_layers > 0 ? p->layers[0].attn_norm : m.final_norm;
-  // full-vocabulary head over rows of `src` in blocks, argmax into generated
-  // slot `step`, the embedding of the next step's row.  A row's scale does not
-  // change its argmax: the steps' rows are the final norm's operand x * g.
-  auto next_tokens = [&](int step, const void* src) -> aiq_status {
+  // full-vocabulary head over hf in row blocks, argmax into generated slot
+  // `step`, the embedding of the next step's row
+  auto next_tokens = [&](int step) -> aiq_status {
     for (int b = 0; b < p->gen_blocks; ++b) {
       const int64_t row0 = static_cast<int64_t>(b) * GEN_HEAD_ROWS;
-      TRACED(tr, AIQ_K_DECODE_HEAD, gemm(EPI_ARGMAX, static_cast<const char*>(src) + row0 * d * ab, d, cnt + b,
+      TRACED(tr, AIQ_K_DECODE_HEAD, gemm(EPI_ARGMAX, static_cast<const char*>(hf) + row0 * d * ab, d, cnt + b,
                                          std::min<int64_t>(su - row0, GEN_HEAD_ROWS), m.vocab, d, m.lm_head,
                                          nullptr, nullptr, logits, m.vocab / 64, nullptr, false));
       GenNextArgs na{};
@@ -758,7 +757,7 @@ aiq_status enqueue_generation(const aiq_plan* p, void* ws, const Layout& L, cons
     }
     return AIQ_OK;
   };
-  aiq_status e = next_tokens(0, hf);
+  aiq_status e = next_tokens(0);
   if (e != AIQ_OK) return e;
   const int64_t* n_rows = gd + D_NTOK;
   const size_t kv_layer = static_cast<size_t>(pu.qkv_rows) * p->n_qkv * ab;
@@ -795,10 +794,11 @@ aiq_status enqueue_generation(const aiq_plan* p, void* ws, const Layout& L, cons
       TRACED(tr, AIQ_K_DECODE, gemm(EPI_SWIGLU, h, d, n_rows, su, 2 * m.d_ff, d, W.w_gate, W.w_up, nullptr, ffn,
                                     m.d_ff, nullptr, false, fold));
       TRACED(tr, AIQ_K_DECODE, gemm(EPI_RESID, ffn, m.d_ff, n_rows, su, d, m.d_ff, W.w_down, nullptr, nullptr,
-                                    nullptr, d, last ? m.final_norm : p->layers[l + 1].attn_norm, true));
+                                    nullptr, d, last ? nullptr : p->layers[l + 1].attn_norm, true));
       if (!last && !fold) TRACED(tr, AIQ_K_DECODE, launch_row_scale(gd, ssp, d / 64, d, eps, rs, su, s));
     }
-    e = next_tokens(k + 1, h);
+    TRACED(tr, AIQ_K_DECODE, launch_norm_rows(gd, x, m.final_norm, d, eps, hf, p->act, su, s));
+    e = next_tokens(k + 1);
     if (e != AIQ_OK) return e;
   }
   return AIQ_OK;

@@ -442,6 +442,9 @@ struct LastRows {
   int32_t* posl;
 };
 hipError_t launch_last_rows(const int64_t* ldesc, const int64_t* cu, const LastRows& a, int64_t R, hipStream_t s);
+// hf[i] = x[i] / rms * g in 16 bits, i < gen_desc[D_NSEQ]
+hipError_t launch_norm_rows(const int64_t* gen_desc, const float* x, const float* g, int32_t d, float eps, void* hf,
+                            int32_t act, int64_t seq_ub, hipStream_t s);
 // Argmax over a block of full-vocabulary rows given as the head GEMM's
 // EPI_ARGMAX partials (int2 [rows][vocab / 64]; ties to the lowest id):
 // row r is sequence i = row0 + r; its token goes to gen[(seq_begin + i) * G +

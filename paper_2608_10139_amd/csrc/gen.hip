@@ -340,11 +340,39 @@ hipError_t launch_attention_gen(const GenAttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// ------------------------------------------------------------------ final norm of the step rows
+// Normalised in fp32, then rounded: the head's 16-bit operand keeps its range
+// and its bits whatever the residual's size (x * g alone overflows fp16 above
+// 65,504 and loses bits below 6e-5).
+__global__ __launch_bounds__(256) void k_norm_rows(const int64_t* gd, const float* x, const float* g, int32_t d,
+                                                   float eps, uint16_t* hf, int32_t act) {
+  const int64_t n = gd[D_NSEQ];
+  const int lane = threadIdx.x & 63;
+  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
+  const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  for (int64_t i = wave; i < n; i += n_waves) {
+    const float* xr = x + i * d;
+    float ss = 0.f;
+    for (int c = lane; c < d; c += 64) ss += xr[c] * xr[c];
+    ss = wave_sum_g(ss);
+    const float r = 1.0f / sqrtf(ss / static_cast<float>(d) + eps);
+    for (int c = lane; c < d; c += 64) hf[i * d + c] = f2act(xr[c] * r * g[c], act);
+  }
+}
+
+hipError_t launch_norm_rows(const int64_t* gen_desc, const float* x, const float* g, int32_t d, float eps, void* hf,
+                            int32_t act, int64_t seq_ub, hipStream_t s) {
+  if (act == ACT_F32) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_norm_rows, dim3(grid_for(seq_ub, 4, 4096)), dim3(256), 0, s, gen_desc, x, g, d, eps,
+                     static_cast<uint16_t*>(hf), act);
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ the next token and its embedding
 // The head GEMM leaves, per row, the maximum and its column over every 64
 // columns (lowest column on ties); a wave per row picks the largest, again
-// the lowest column among equals, records the token and, unless the row's
-// generation is over, writes the token's embedding for the next step (x, the
+// the lowest column among equals, records the token and, but in the last step
+// (also for rows that have ended, whose tokens are pads), writes the token's embedding for the next one (x, the
 // first norm's operand h = x * g, its row scale, the position): one launch where the
 // argmax and the embedding took 5 us each.
 __global__ __launch_bounds__(256) void k_gen_next(GenNextArgs a) {
