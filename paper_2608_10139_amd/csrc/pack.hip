@@ -319,11 +319,18 @@ __global__ __launch_bounds__(256) void k_embed_norm(const int64_t* desc, const i
       }
     }
     int64_t sq = seq_of(cu, sb, ns, tb + t0, lane);
-    if (lane < n) {
-      const int64_t gt = tb + t0 + lane;
-      while (sq + 1 < sb + ns && cu[sq + 1] <= gt) ++sq;   // at most EMB_RUN - 1 tokens on (empty lists skipped)
-      pos[t0 + lane] = pos_base + static_cast<int32_t>(gt - cu[sq]);
+    const int64_t gt = tb + t0 + lane;
+    bool far = false;
+    if (lane < n) {   // a few sequences on, else a search of its own (a run of empty lists may lie between)
+      for (int k = 0; k < EMB_RUN && sq + 1 < sb + ns && cu[sq + 1] <= gt; ++k) ++sq;
+      far = sq + 1 < sb + ns && cu[sq + 1] <= gt;
     }
+    for (uint64_t left = __ballot(far); left; left &= left - 1) {
+      const int u = __ffsll(static_cast<unsigned long long>(left)) - 1;
+      const int64_t found = seq_of(cu, sb, ns, tb + t0 + u, lane);
+      if (lane == u) sq = found;
+    }
+    if (lane < n) pos[t0 + lane] = pos_base + static_cast<int32_t>(gt - cu[sq]);
     const uint16_t* er[EMB_RUN];
     float ssq[EMB_RUN];
 #pragma unroll

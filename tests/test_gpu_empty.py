@@ -138,3 +138,57 @@ def test_trailing_empty_rows_are_classified(npre, chunk_tokens):
     one = run(t, m, dm, q)   # one chunk: bit-identical
     np.testing.assert_array_equal(r["logits"], one["logits"])
     np.testing.assert_array_equal(r["kept_ids"], one["kept_ids"])
+
+
+def _spread_table(lists, gaps):
+    """Row i holds lists[i] and is followed by gaps[i] rows with empty lists;
+    every row selected by c >= 0.  Returns the tables and the full rows' ids."""
+    lens = np.concatenate([np.concatenate([[len(v)], np.zeros(g, np.int64)]) for v, g in zip(lists, gaps)])
+    off = np.zeros(len(lens) + 1, dtype=np.int64)
+    off[1:] = np.cumsum(lens)
+    n = len(lens)
+    probe = {"id": np.arange(n, dtype=np.int32), "c": np.zeros(n, np.int32), "offsets": off,
+             "tokens": np.concatenate(lists).astype(np.int32)}
+    ids = np.concatenate([[0], np.cumsum(np.asarray(gaps) + 1)[:-1]])
+    return {"probe": probe, "build": None, "prefix": np.zeros(0, np.int32)}, ids
+
+
+def _logits_and_ms(m, dm, lists, gaps):
+    t, ids = _spread_table(lists, gaps)
+    q = Query(preds=(Pred("c", "ge", 0),), labels=(1, 2), decision="binary_gt", agg="count")
+    dq = DeviceQuery(t, m, q, dmodel=dm)
+    ms = []
+    for _ in range(3):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        dq.run()
+        b.record()
+        torch.cuda.synchronize()
+        ms.append(a.elapsed_time(b))
+    r = dq.results()
+    dq.close()
+    assert r["status"] == 0 and r["n_selected"] == len(t["probe"]["id"])
+    empty = np.setdiff1d(np.arange(r["n_selected"]), ids)
+    assert np.all(r["logits"][empty] == 0.0)
+    return r["logits"][ids], min(ms)
+
+
+def test_empty_rows_between_the_tokens_of_one_wave():
+    """The embedding takes runs of consecutive tokens; lists of one token with
+    0 .. 5,000 empty rows between them keep their logits, and 200,000 empty
+    rows between two tokens cost what they cost behind the last one."""
+    say("case: runs of empty rows between tokens")
+    m, dm = model("bf16")
+    r = np.random.default_rng(21)
+    gaps = [0, 1, 2, 3, 4, 5, 0, 6, 70, 0, 5000, 1, 1, 64, 65, 3]
+    lists = [r.integers(3, 1000, 1 + (i % 5 == 4) * 6) for i in range(len(gaps))]
+    none, _ = _logits_and_ms(m, dm, lists, [0] * len(gaps))
+    got, _ = _logits_and_ms(m, dm, lists, gaps)
+    np.testing.assert_array_equal(got, none)
+    lists = [r.integers(3, 1000, 1) for _ in range(8)]
+    behind, ms_behind = _logits_and_ms(m, dm, lists, [0] * 7 + [200000])
+    between, ms_between = _logits_and_ms(m, dm, lists, [0] * 4 + [1, 199999] + [0] * 2)
+    say(f"  200,000 empty rows behind the tokens {ms_behind:.2f} ms, between them {ms_between:.2f} ms")
+    np.testing.assert_array_equal(between, behind)
+    # one lane walking them in dependent loads takes 21 ms more
+    assert ms_between < 1.5 * ms_behind + 5.0
