@@ -209,8 +209,8 @@ void take_last(const aiq_plan* p, Carver& c, Layout& L, int64_t seq) {
   if (!p->prune_last) return;
   L.xl = c.take(static_cast<size_t>(last_rows(seq)) * p->model.d_model * 4);
   L.ldesc = c.take(static_cast<size_t>(last_blocks(seq)) * D_STRIDE * 8);
-  // row scales and positions of the last positions (GEMM tiles read 256 rows)
-  if (p->q_last_only) L.laux = c.take(static_cast<size_t>(last_rows(seq) + 256) * 8);
+  // row scales and positions of the last positions of every block (GEMM tiles read 256 rows)
+  if (p->q_last_only) L.laux = c.take(static_cast<size_t>(std::max<int64_t>(seq, 1) + 256) * 8);
 }
 
 Layout run_layout(const aiq_plan* p) {
@@ -551,28 +551,41 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
         float* xl = at<float>(ws, L.xl);
         const size_t hf_row = static_cast<size_t>(d) * (p->act ? 2 : 4);
         const bool fold_r = R <= RS_FOLD_ROWS;
+        // the last positions' residual rows and, for their queries alone, their
+        // h rows, row scales and positions
+        LastRows lr{};
+        lr.x = x;
+        lr.xl = xl;
+        lr.d = d;
+        lr.eps = eps;
+        auto queries = [&](int32_t b) {   // block b's part of att (rows below t_cap), row scales and positions
+          lr.h = h;
+          lr.rs = rs;
+          lr.ssp = fold && l > 0 ? ssp : nullptr;
+          lr.pos = pos;
+          lr.hl = static_cast<char*>(att) + static_cast<size_t>(b) * R * d * act_bytes(p);
+          lr.rsl = at<float>(ws, L.laux) + static_cast<int64_t>(b) * R;
+          lr.posl = reinterpret_cast<int32_t*>(lr.rsl + std::max<int64_t>(seq_ub, 1) + 256);
+        };
+        // a block's projections write h, ssp and rs from row 0 on, where rows of
+        // later blocks may lie (behind sequences without tokens): with more than
+        // one block all of them are gathered first
+        const bool ahead = p->q_last_only && nb > 1;
+        for (int32_t b = 0; ahead && b < nb; ++b) {
+          queries(b);
+          LastRows lh = lr;
+          lh.x = nullptr;
+          TRACED(tr, AIQ_K_LAST, launch_last_rows(ldesc + static_cast<int64_t>(b) * D_STRIDE, cu, lh, R, s));
+        }
         for (int32_t b = 0; b < nb; ++b) {
           const int64_t* bd = ldesc + static_cast<int64_t>(b) * D_STRIDE;
           GenAttnArgs ga{};
-          // the last positions' residual rows and, for their queries alone,
-          // their h rows, row scales and positions
-          LastRows lr{};
-          lr.x = x;
-          lr.xl = xl;
-          lr.d = d;
-          lr.eps = eps;
-          if (p->q_last_only) {
-            lr.h = h;
-            lr.rs = rs;
-            lr.ssp = fold && l > 0 ? ssp : nullptr;
-            lr.pos = pos;
-            lr.hl = att;
-            lr.rsl = at<float>(ws, L.laux);
-            lr.posl = reinterpret_cast<int32_t*>(lr.rsl + R + 256);
-          }
-          TRACED(tr, AIQ_K_LAST, launch_last_rows(bd, cu, lr, R, s));
+          if (p->q_last_only) queries(b);
+          LastRows lx = lr;
+          if (ahead) lx.hl = nullptr;
+          TRACED(tr, AIQ_K_LAST, launch_last_rows(bd, cu, lx, R, s));
           if (p->q_last_only) {   // the q projection (rotary) into ffn
-            TRACED(tr, AIQ_K_LAST, gemm_part(att, bd + D_NTOK, R, p->d_q, p->d_q, 0, W.wq, W.wk, W.wv, ffn, p->d_q,
+            TRACED(tr, AIQ_K_LAST, gemm_part(lr.hl, bd + D_NTOK, R, p->d_q, p->d_q, 0, W.wq, W.wk, W.wv, ffn, p->d_q,
                                              lr.rsl, lr.posl, false));
             ga.qkv = ffn;
             ga.ldq = p->d_q;

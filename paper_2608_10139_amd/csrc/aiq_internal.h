@@ -423,7 +423,7 @@ struct GenAttnArgs {
   int64_t ldq;
 };
 hipError_t launch_attention_gen(const GenAttnArgs& a, hipStream_t s);
-// The last position of sequence i (i < ldesc[D_NSEQ]): its residual row x (d
+// The last position of sequence i (i < ldesc[D_NSEQ]): with x, its residual row (d
 // fp32 values) into row i of xl and, with hl, its 16-bit normalised row h, row
 // scale and position into row i of hl, rsl and posl; the scale from rs, or with ssp
 // from the row's sums of squares (as launch_row_scale).  Sequences with no own

@@ -66,9 +66,11 @@ __global__ __launch_bounds__(256) void k_last_rows(const int64_t* ld, const int6
     const int64_t c1 = cu[sb + i + 1];
     if (c1 == cu[sb + i]) continue;
     const int64_t r = c1 - 1 - tb;
-    const float4* src = reinterpret_cast<const float4*>(a.x + r * d);
-    float4* dst = reinterpret_cast<float4*>(a.xl + i * d);
-    for (int c = lane; c < d / 4; c += 64) dst[c] = src[c];
+    if (a.x) {
+      const float4* src = reinterpret_cast<const float4*>(a.x + r * d);
+      float4* dst = reinterpret_cast<float4*>(a.xl + i * d);
+      for (int c = lane; c < d / 4; c += 64) dst[c] = src[c];
+    }
     if (!a.hl) continue;
     const uint4* hs = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.h) + r * d);
     uint4* hd = reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.hl) + i * d);

@@ -192,3 +192,16 @@ def test_empty_rows_between_the_tokens_of_one_wave():
     np.testing.assert_array_equal(between, behind)
     # one lane walking them in dependent loads takes 21 ms more
     assert ms_between < 1.5 * ms_behind + 5.0
+
+
+def test_empty_rows_before_a_later_block_of_last_positions():
+    """More sequences than one block of last positions (262,144): the rows of
+    the second block come early in the packed batch, where the first block's
+    own rows would lie."""
+    say("case: 262,300 empty rows between two rows with tokens")
+    m, dm = model("bf16")
+    r = np.random.default_rng(22)
+    lists = [r.integers(3, 1000, int(n)) for n in r.integers(1, 30, 40)]
+    behind, _ = _logits_and_ms(m, dm, lists, [0] * 39 + [262300])
+    between, _ = _logits_and_ms(m, dm, lists, [262300] + [0] * 39)
+    np.testing.assert_array_equal(between, behind)
