@@ -354,60 +354,70 @@ hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s) {
 }
 
 // ======================================================================= fp32
-// One workgroup per (sequence, head) item.  Four neighbouring lanes share a
-// query of the 64-query block, each taking every fourth key of the staged
-// 64-key block: scores of its 16 keys first, then one online-softmax update
-// for all of them, and the four partial states merge at the end.  (One lane per
-// query walking all keys one by one left 64 threads per item and a chain of
-// 64 dependent updates per block: 50 us for 153 sequences of 35 tokens and 4
-// heads of 32; this takes 14 us.)
-template <int HD>
-__global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
+// Four neighbouring lanes share a query, each taking every fourth key of the
+// staged 64-key block: scores of its keys first, then one online-softmax
+// update for all of them against the maximum of the four lanes, whose sums meet at
+// the end.  (One lane per query walking all keys one by one left 64 threads per
+// item and a chain of 64 dependent updates per block: 50 us for 153 sequences of 35
+// tokens and 4 heads of 32; this takes 14 us.)
+//
+// SOLO: a wave does an item of at most 16 positions by itself (keys in its own 16
+// rows of LDS); else four waves take 16 queries each of 64-query blocks.  Both do the same
+// operations for a query, in the same order.
+template <int HD, bool SOLO>
+__device__ __forceinline__ void attn_f32_item(const AttnArgs& a, int64_t s0, int L, int h, int kvh, float* Ks,
+                                              float* Vs) {
   constexpr int P = HD + 4;   // row pitch: the four keys read at once lie in different banks
-  constexpr int KT = 16;      // keys per lane and block
-  __shared__ __attribute__((aligned(16))) float Ks[64 * P];
-  __shared__ __attribute__((aligned(16))) float Vs[64 * P];
-  const int64_t tb = a.desc[D_TOK_BEGIN], sb = a.desc[D_SEQ_BEGIN], ns = a.desc[D_NSEQ];
-  const int64_t n_items = ns * a.n_heads;
-  const int t = threadIdx.x, part = t & 3;
-  const int rep = a.n_heads / a.n_kv;
+  constexpr int KT = SOLO ? 4 : 16;   // keys per lane and block
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = lane & 3;
   const int d_q = a.n_heads * HD, d_kv = a.n_kv * HD;
   const float scale = 1.0f / sqrtf(static_cast<float>(HD));
   const float* qkv = static_cast<const float*>(a.qkv);
   float* out = static_cast<float*>(a.out);
-  for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-    const int64_t si = item / a.n_heads;
-    const int h = static_cast<int>(item % a.n_heads);
-    const int kvh = h / rep;
-    const int64_t s0 = a.cu[sb + si] - tb;
-    const int L = static_cast<int>(a.cu[sb + si + 1] - a.cu[sb + si]);
-    for (int qb = 0; qb * 64 < L; ++qb) {
-      const int qi = qb * 64 + (t >> 2);
-      f32x4 q[HD / 4], o[HD / 4];
+  const int t = SOLO ? lane : static_cast<int>(threadIdx.x);
+  for (int qb = 0; SOLO ? qb < 1 : qb * 64 < L; ++qb) {
+    const int q0 = qb * 64 + (SOLO ? 0 : w * 16);   // the wave's first query
+    const int qi = q0 + (lane >> 2);
+    f32x4 q[HD / 4], o[HD / 4];
 #pragma unroll
-      for (int i = 0; i < HD / 4; ++i) {
-        q[i] = qi < L ? *reinterpret_cast<const f32x4*>(qkv + (s0 + qi) * a.ld + h * HD + 4 * i) : f32x4{0.f, 0.f, 0.f, 0.f};
-        o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-      float m = -INFINITY, l = 0.f;
-      for (int kb = 0; kb <= qb; ++kb) {
-        __syncthreads();
-        for (int id = t; id < 64 * HD / 4; id += 256) {
-          const int r = id / (HD / 4), c = (id % (HD / 4)) * 4;
-          const int kk = kb * 64 + r;
-          f32x4 kv = f32x4{0.f, 0.f, 0.f, 0.f}, vv = kv;
-          if (kk < L) {
-            const float* row = qkv + (s0 + kk) * a.ld + d_q + kvh * HD + c;
-            kv = *reinterpret_cast<const f32x4*>(row);
-            vv = *reinterpret_cast<const f32x4*>(row + d_kv);
-          }
-          *reinterpret_cast<f32x4*>(Ks + r * P + c) = kv;
-          *reinterpret_cast<f32x4*>(Vs + r * P + c) = vv;
+    for (int i = 0; i < HD / 4; ++i) {
+      q[i] = qi < L ? *reinterpret_cast<const f32x4*>(qkv + (s0 + qi) * a.ld + h * HD + 4 * i) : f32x4{0.f, 0.f, 0.f, 0.f};
+      o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    float m = -INFINITY, l = 0.f;
+    for (int kb = 0; kb <= qb; ++kb) {
+      const int nk = L - kb * 64 < 64 ? L - kb * 64 : 64;   // keys of the block; rows up to the next 16 are zeroed
+      if (!SOLO) __syncthreads();
+      for (int id = t; id < ((nk + 15) & ~15) * (HD / 4); id += SOLO ? 64 : 256) {
+        const int r = id / (HD / 4), c = (id % (HD / 4)) * 4;
+        f32x4 kv = f32x4{0.f, 0.f, 0.f, 0.f}, vv = kv;
+        if (r < nk) {
+          const float* row = qkv + (s0 + kb * 64 + r) * a.ld + d_q + kvh * HD + c;
+          kv = *reinterpret_cast<const f32x4*>(row);
+          vv = *reinterpret_cast<const f32x4*>(row + d_kv);
         }
+        *reinterpret_cast<f32x4*>(Ks + r * P + c) = kv;
+        *reinterpret_cast<f32x4*>(Vs + r * P + c) = vv;
+      }
+      if (SOLO) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      } else {
         __syncthreads();
-        float s[KT], mx = -INFINITY;
+      }
+      if (q0 >= L) continue;   // no query of this wave (the barriers above are met all the same)
+      // keys up to the wave's last query, in groups of 16
+      const int last = (q0 + 15 < L ? q0 + 15 : L - 1) - kb * 64;
+      const int nw = last + 1 < nk ? last + 1 : nk;
+      float s[KT], mx = -INFINITY;
 #pragma unroll
-        for (int j = 0; j < KT; ++j) {
+      for (int g = 0; g < KT; g += 4) {
+#pragma unroll
+        for (int j = g; j < g + 4; ++j) s[j] = -INFINITY;
+        if (!SOLO && 4 * g >= nw) continue;
+#pragma unroll
+        for (int j = g; j < g + 4; ++j) {
           const int r = 4 * j + part, key = kb * 64 + r;
           float dot = 0.f;
 #pragma unroll
@@ -416,20 +426,24 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) dot = fmaf(q[i][e], kv[e], dot);
           }
-          s[j] = key <= qi && key < L ? dot * scale : -INFINITY;
+          if (key <= qi && key < L) s[j] = dot * scale;
           mx = fmaxf(mx, s[j]);
         }
-        // none of this lane's keys precede the query: told by position, since
-        // fmaxf drops NaN and a NaN score has to reach l and o
-        if (kb * 64 + part > qi) continue;
-        const float m_new = fmaxf(m, mx);
-        const float ref = m_new == -INFINITY ? 0.f : m_new;   // no finite score yet: weights are 0 or NaN
-        const float alpha = expf(m - ref);
-        l *= alpha;
+      }
+      mx = fmaxf(mx, dpp_f32<0xB1>(mx));   // the query's four lanes
+      mx = fmaxf(mx, dpp_f32<0x4E>(mx));
+      const float m_new = fmaxf(m, mx);
+      // fmaxf drops NaN: without a finite score the weights are NaN, or 0 against reference 0
+      const float ref = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = expf(m - ref);
+      l *= alpha;
 #pragma unroll
-        for (int i = 0; i < HD / 4; ++i) o[i] *= alpha;
+      for (int i = 0; i < HD / 4; ++i) o[i] *= alpha;
 #pragma unroll
-        for (int j = 0; j < KT; ++j) {
+      for (int g = 0; g < KT; g += 4) {
+        if (!SOLO && 4 * g >= nw) continue;
+#pragma unroll
+        for (int j = g; j < g + 4; ++j) {
           const float pr = expf(s[j] - ref);   // 0 for keys after the query
           l += pr;
 #pragma unroll
@@ -439,28 +453,66 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
             for (int e = 0; e < 4; ++e) o[i][e] = fmaf(pr, vv[e], o[i][e]);
           }
         }
-        m = m_new;
       }
-      // merge the four partial states; 0 * NaN keeps a NaN of a lane without a finite score
-      float mm = fmaxf(m, __shfl_xor(m, 1));
-      mm = fmaxf(mm, __shfl_xor(mm, 2));
-      const float wgt = m == -INFINITY ? 0.f : expf(m - mm);
-      l *= wgt;
-      l += __shfl_xor(l, 1);
-      l += __shfl_xor(l, 2);
+      m = m_new;
+    }
+    if (q0 < L) {   // the sums of the four lanes
+      l += dpp_f32<0xB1>(l);
+      l += dpp_f32<0x4E>(l);
       const float inv = 1.0f / l;
       float* orow = out + (s0 + qi) * a.ldo + h * HD;
 #pragma unroll
       for (int i = 0; i < HD / 4; ++i) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          float v = o[i][e] * wgt;
-          v += __shfl_xor(v, 1);
-          v += __shfl_xor(v, 2);
+          float v = o[i][e];
+          v += dpp_f32<0xB1>(v);
+          v += dpp_f32<0x4E>(v);
           o[i][e] = v * inv;
         }
         if (qi < L && (i & 3) == part) *reinterpret_cast<f32x4*>(orow + 4 * i) = o[i];
       }
+    }
+  }
+}
+
+// One item is a (sequence, head).  Where items are many (at least four per
+// workgroup) a workgroup takes four of them: the short ones a wave each, the
+// others one after another with all waves.  Two tokens each, 100,000 sequences, 4 heads
+// of 32: 9.9 ms with all waves on every item and no bound on the keys, 1.3 ms with this.
+template <int HD>
+__global__ __launch_bounds__(256, HD == 32 ? 3 : 2) void k_attn_f32(AttnArgs a) {
+  constexpr int P = HD + 4;
+  __shared__ __attribute__((aligned(16))) float Ks[64 * P];
+  __shared__ __attribute__((aligned(16))) float Vs[64 * P];
+  const int64_t tb = a.desc[D_TOK_BEGIN], sb = a.desc[D_SEQ_BEGIN], ns = a.desc[D_NSEQ];
+  const int64_t n_items = ns * a.n_heads;
+  const int rep = a.n_heads / a.n_kv;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int per = n_items >= 4 * static_cast<int64_t>(gridDim.x) ? 4 : 1;
+  for (int64_t item0 = static_cast<int64_t>(blockIdx.x) * per; item0 < n_items;
+       item0 += static_cast<int64_t>(gridDim.x) * per) {
+    if (per > 1) {
+      __syncthreads();   // the joint items before are done with the keys
+      const int64_t item = item0 + w;
+      if (item < n_items) {
+        const int64_t si = item / a.n_heads;
+        const int h = static_cast<int>(item - si * a.n_heads);
+        const int64_t c0 = a.cu[sb + si];
+        const int L = static_cast<int>(a.cu[sb + si + 1] - c0);
+        if (L <= 16)
+          attn_f32_item<HD, true>(a, c0 - tb, L, h, h / rep, Ks + w * 16 * P, Vs + w * 16 * P);
+      }
+    }
+    for (int j = 0; j < per; ++j) {
+      const int64_t item = item0 + j;
+      if (item >= n_items) break;
+      const int64_t si = item / a.n_heads;
+      const int h = static_cast<int>(item - si * a.n_heads);
+      const int64_t c0 = a.cu[sb + si];
+      const int L = static_cast<int>(a.cu[sb + si + 1] - c0);
+      if (per > 1 && L <= 16) continue;
+      attn_f32_item<HD, false>(a, c0 - tb, L, h, h / rep, Ks, Vs);
     }
   }
 }

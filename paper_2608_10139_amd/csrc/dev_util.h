@@ -22,6 +22,14 @@ __device__ __forceinline__ float h2f(uint16_t h) { return static_cast<float>(__b
 __device__ __forceinline__ uint16_t f2act(float f, int act) { return act == ACT_F16 ? f2h(f) : f2bf(f); }
 __device__ __forceinline__ float act2f(uint16_t v, int act) { return act == ACT_F16 ? h2f(v) : bf2f(v); }
 
+// Lane exchange through a DPP move (a VALU op; a lane shuffle goes through
+// the LDS crossbar): 0xB1 lane ^ 1, 0x4E lane ^ 2, 0x141 the mirrored quad of
+// eight lanes.
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
 // RMSNorm scale of a row from its n_part sums of squares (n_part % 4 == 0,
 // 16-byte aligned), added in order.
 __device__ __forceinline__ float row_scale(const float* p, int n_part, int d, float eps) {

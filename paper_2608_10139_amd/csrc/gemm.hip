@@ -123,15 +123,10 @@ typedef f32x16_t f32x16;
 // q, k and v (attention operands) are stored in fp16: 10 mantissa bits where
 // bf16 has 7, at the same MFMA rate; their magnitudes are O(1) after RMSNorm.
 
-// Lane exchange through a DPP move (a VALU op; a lane shuffle goes through
-// the LDS crossbar).  The residual epilogue's butterfly takes the same
+// The residual epilogue's butterfly of DPP moves (dpp_f32) takes the same
 // partners and adds in the same order as lane ^ 1, ^ 2, ^ 4 shuffles: after
 // the first two steps the four lanes of a quad hold equal sums, so the
 // mirrored quad is the ^ 4 partner's.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
-}
 
 __device__ __forceinline__ float silu_fast(float g) {
   return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
