@@ -152,10 +152,13 @@ hipError_t launch_row_scale(const int64_t* desc, const float* ssp, int32_t n_par
 // scale 1 / rms is applied to the sums), a second over the row for hf_out.
 // With one wave per sequence and 4-byte loads in a chain per label the head of 8
 // sequences of d 3072 took 55 us; this takes 10 (128 of d 2048: 45, 9).
+// NW waves, as many as a row's float4 pieces occupy (at most four; idle ones cost
+// many sequences their barriers: 100,000 of d 128 268 us with four, 20,000 of d 512 56 and 30).
 // label_out / logits_out are indexed by the global
 // sequence number (seq_begin + local index).
-__global__ __launch_bounds__(256) void k_head(HeadArgs a) {
-  __shared__ float red[4][AIQ_MAX_LABELS + 1];
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_head(HeadArgs a) {
+  __shared__ float red[NW][AIQ_MAX_LABELS + 1];
   const int64_t tb = a.desc[D_TOK_BEGIN], sb = a.desc[D_SEQ_BEGIN], ns = a.desc[D_NSEQ];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int d = a.d;
@@ -185,7 +188,7 @@ __global__ __launch_bounds__(256) void k_head(HeadArgs a) {
     float ss = 0.f, acc[AIQ_MAX_LABELS];
 #pragma unroll
     for (int k = 0; k < AIQ_MAX_LABELS; ++k) acc[k] = 0.f;
-    for (int c = t * 4; c < d; c += 1024) {
+    for (int c = t * 4; c < d; c += 256 * NW) {
       const float4 x = xv(c), g = *reinterpret_cast<const float4*>(a.g + c);
       ss += (x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w);
 #pragma unroll
@@ -204,18 +207,34 @@ __global__ __launch_bounds__(256) void k_head(HeadArgs a) {
       }
     }
     ss = wave_sum(ss);
-    if (lane == 0) red[w][AIQ_MAX_LABELS] = ss;
 #pragma unroll
     for (int k = 0; k < AIQ_MAX_LABELS; ++k) {
       if (k >= a.n_labels) break;
-      const float v = wave_sum(acc[k]);
-      if (lane == 0) red[w][k] = v;
+      acc[k] = wave_sum(acc[k]);
     }
-    __syncthreads();
-    auto total = [&](int k) { return (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]); };
-    const float r = empty ? 0.f : 1.0f / sqrtf(total(AIQ_MAX_LABELS) / static_cast<float>(d) + a.eps);
+    if (NW > 1) {
+      if (lane == 0) {
+        red[w][AIQ_MAX_LABELS] = ss;
+#pragma unroll
+        for (int k = 0; k < AIQ_MAX_LABELS; ++k) {
+          if (k >= a.n_labels) break;
+          red[w][k] = acc[k];
+        }
+      }
+      __syncthreads();
+      auto total = [&](int k) {
+        return NW == 2 ? red[0][k] + red[1][k] : (red[0][k] + red[1][k]) + (red[NW - 2][k] + red[NW - 1][k]);
+      };
+      ss = total(AIQ_MAX_LABELS);
+#pragma unroll
+      for (int k = 0; k < AIQ_MAX_LABELS; ++k) {
+        if (k >= a.n_labels) break;
+        acc[k] = total(k);
+      }
+    }
+    const float r = empty ? 0.f : 1.0f / sqrtf(ss / static_cast<float>(d) + a.eps);
     if (a.hf_out) {
-      for (int c = t * 4; c < d; c += 1024) {
+      for (int c = t * 4; c < d; c += 256 * NW) {
         const float4 x = xv(c), g = *reinterpret_cast<const float4*>(a.g + c);
         const float4 o = make_float4(x.x * r * g.x, x.y * r * g.y, x.z * r * g.z, x.w * r * g.w);
         if (a.hf_act != ACT_F32) {
@@ -233,7 +252,7 @@ __global__ __launch_bounds__(256) void k_head(HeadArgs a) {
 #pragma unroll
       for (int k = 0; k < AIQ_MAX_LABELS; ++k) {
         if (k >= a.n_labels) break;
-        lg[k] = total(k) * r;
+        lg[k] = acc[k] * r;
         if (a.logits_out) a.logits_out[gi * a.n_labels + k] = lg[k];
       }
       if (a.label_out) {
@@ -256,13 +275,18 @@ __global__ __launch_bounds__(256) void k_head(HeadArgs a) {
         a.label_out[gi] = lab;
       }
     }
-    __syncthreads();   // the partial sums are read before the next sequence writes them
+    if (NW > 1) __syncthreads();   // the partial sums are read before the next sequence writes them
   }
 }
 
 hipError_t launch_head(const HeadArgs& a, hipStream_t s) {
   if (a.d % 4) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_head, dim3(grid_for(a.seq_ub, 1, 4096)), dim3(256), 0, s, a);
+  if (a.d <= 256)
+    hipLaunchKernelGGL(k_head<1>, dim3(grid_for(a.seq_ub, 1, 16384)), dim3(64), 0, s, a);
+  else if (a.d <= 512)
+    hipLaunchKernelGGL(k_head<2>, dim3(grid_for(a.seq_ub, 1, 8192)), dim3(128), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_head<4>, dim3(grid_for(a.seq_ub, 1, 4096)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
