@@ -11,6 +11,18 @@ TOL_F32 = 1e-4   # |logit difference| bound for fp32 models
 TOL_BF16 = 2e-2  # ... and for bf16 models
 
 
+def random_gains(m, seed=7):
+    """The model with a gain of its own in 0.5 .. 1.5 for every norm and column
+    (make_model's are all one, which hides a gain read at a wrong place)."""
+    r = np.random.default_rng(seed)
+    d = m["spec"].d_model
+    for lw in m["layers"]:
+        for k in ("attn_norm", "ffn_norm"):
+            lw[k] = r.uniform(0.5, 1.5, d).astype(np.float32)
+    m["final_norm"] = r.uniform(0.5, 1.5, d).astype(np.float32)
+    return m
+
+
 def load_golden(name):
     path = os.path.join(GOLDEN, f"{name}_oracle.npz")
     if not os.path.exists(path):

@@ -10,7 +10,7 @@ import oracle
 from paper_2608_10139_amd.device import DeviceModel, DevicePrefill
 from synth.configs import ModelSpec
 from synth.gen import make_model
-from tests._parity import TOL_F32
+from tests._parity import TOL_F32, random_gains
 
 pytestmark = pytest.mark.gpu
 
@@ -30,7 +30,7 @@ def run(dm, batch):
 def test_f32_model(d, heads, kv, ff):
     spec = ModelSpec(n_layers=2, d_model=d, n_heads=heads, n_kv_heads=kv, d_ff=ff, vocab=256, act="gelu", dtype="f32",
                      weight_seed=61, init_std=0.05)
-    m = make_model(spec)
+    m = random_gains(make_model(spec))
     dm = DeviceModel(m)
     r = np.random.default_rng(3)
     seqs = [r.integers(0, 256, n).astype(np.int32)

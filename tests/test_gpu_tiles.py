@@ -13,7 +13,7 @@ import oracle
 from paper_2608_10139_amd.device import DeviceModel, DevicePrefill
 from synth.configs import ModelSpec
 from synth.gen import make_model
-from tests._parity import TOL_BF16
+from tests._parity import TOL_BF16, random_gains
 
 pytestmark = pytest.mark.gpu
 
@@ -31,7 +31,7 @@ _M = {}
 
 def model(name, compute):
     if (name, compute) not in _M:
-        m = make_model(MODELS[name])
+        m = random_gains(make_model(MODELS[name]))
         _M[name, compute] = (m, DeviceModel(m, compute=compute))
     return _M[name, compute]
 
