@@ -14,6 +14,8 @@
 #include "aiq_internal.h"
 #include "dev_util.h"
 
+#include <type_traits>
+
 namespace aiq {
 
 static int grid_for(int64_t n, int per_block, int cap) {
@@ -93,17 +95,16 @@ hipError_t launch_last_rows(const int64_t* ldesc, const int64_t* cu, const LastR
 // the group against every kept key of the sequence (prompt, earlier generated
 // tokens, this token).  A key row of HD fp16 values is read by LPK = HD / 8
 // lanes, 16 bytes each, so one wave load covers 64 / LPK whole rows; keys go
-// in blocks of 4 such loads, block b to wave b mod 4 (no second block in flight:
+// in blocks of 4 such loads, block b to share b mod 4, a share per wave (no second block in flight:
 // its registers cost more in waves per SIMD, 3 for 5, than it hides).  Every lane group keeps its own
 // running maximum and sum over the keys it reads, so a block needs no exchange
 // between lanes but its dot products over the LPK lanes of a row (DPP moves);
-// groups, then waves, merge at the end.  Bound: HBM for many sequences (each
+// groups, then shares, merge at the end.  Bound: HBM for many sequences (each
 // kept key and value row once), the chain of blocks for few.  One wave per
 // item with the maximum and the sum of every block reduced over the wave
 // through the LDS crossbar took 32 us per step for 256 sequences of 170 keys
 // (8 heads of 64) and 98 us for 8 sequences of up to 560 (groups of 3, heads of
-// 128); this takes 23 and 21 us (and 231 us against 228 for 3,276 sequences and groups
-// of 1, at 4.1 TB/s).  The split depends on the keys alone, so a sequence's
+// 128); this takes 23 and 21 us.  The split depends on the keys alone, so a sequence's
 // bits do not depend on the batch.  The workgroup also stores this step's key and
 // value into the generated cache.
 __device__ __forceinline__ float dpp_add(float v, int lanes) {
@@ -127,16 +128,24 @@ __device__ __forceinline__ float across_groups(float v, F f) {
   return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+// Items from which on waves take them alone (groups of up to 3; wider ones keep a wave busy
+// with registers).  8 heads of 64, alone against a workgroup per item: 800 items of 8 / 40 / 170
+// keys 3.8 / 5.2 / 11.7 us against 4.4 / 5.3 / 9.9; 2,000 items 4.2 / 7.6 / 17.1 against
+// 7.4 / 9.2 / 17.5; 160,000 items of 2 / 33 keys 106 / 292 against 323 / 452.
+// Groups of 3, heads of 128: 2,000 items 9.1 / 16.7 / 41.8 against 14.2 / 18.0 / 45.7.
+constexpr int64_t GEN_ALONE_ITEMS = 2000;
+
 template <int HD, int REP>
 __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
   constexpr int LPK = HD / 8;     // lanes per key row
   constexpr int KPI = 64 / LPK;   // key rows per wave load
   constexpr int IT = 4;           // wave loads per block
   constexpr int KB = KPI * IT;    // keys per block
-  constexpr int NW = 4;           // waves per item
-  __shared__ float so[NW][REP][HD], sm[NW][REP], sl[NW][REP];
+  constexpr int NW = 4;           // waves per workgroup, shares per item
+  constexpr bool ALONE = REP <= 3;
+  __shared__ float so_[ALONE ? NW * NW : NW][REP][HD], sm_[ALONE ? NW * NW : NW][REP], sl_[ALONE ? NW * NW : NW][REP];
   const int64_t n = a.gen_desc[D_NSEQ], sb = a.gen_desc[D_SEQ_BEGIN], tb = a.chunk_desc[D_TOK_BEGIN];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, gk = lane / LPK, c = lane % LPK;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), gk = lane / LPK, c = lane % LPK;
   const int d_q = a.n_heads * HD, d_kv = a.n_kv * HD;
   const float scale = 1.4426950408889634f / sqrtf(static_cast<float>(HD));   // log2(e) / sqrt(hd)
   const uint16_t* qkv = static_cast<const uint16_t*>(a.qkv);
@@ -146,21 +155,38 @@ __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
   uint16_t* out = static_cast<uint16_t*>(a.out);
   const int64_t ld = a.ld;
   const int64_t items = n * a.n_kv;
+  // Where items are many, each wave takes items by itself, their shares one
+  // after another: the same sums without waiting for the other waves.
+  const bool alone = ALONE && items >= GEN_ALONE_ITEMS;
+  const int per_wg = alone ? NW : 1;
+  float (*const so)[REP][HD] = so_ + (alone ? NW * w : 0);
+  float (*const sm)[REP] = sm_ + (alone ? NW * w : 0);
+  float (*const sl)[REP] = sl_ + (alone ? NW * w : 0);
+  auto sync = [&]() {
+    if (alone) {   // LDS is in order within a wave
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+      __syncthreads();
+    }
+  };
 
-  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
-    const int64_t i = item / a.n_kv;
-    const int kvh = static_cast<int>(item % a.n_kv);
+  for (int64_t item = static_cast<int64_t>(blockIdx.x) * per_wg + (alone ? w : 0); item < items;
+       item += static_cast<int64_t>(gridDim.x) * per_wg) {
+    const int64_t i = item <= INT32_MAX ? static_cast<int32_t>(item) / a.n_kv : item / a.n_kv;
+    const int kvh = static_cast<int>(item - i * a.n_kv);
     const int64_t s0 = a.cu[sb + i] - tb;
     const int own = static_cast<int>(a.cu[sb + i + 1] - a.cu[sb + i]);
     const int P = a.npre + own;   // prompt positions
-    if (a.last_row && own == 0) continue;   // no own row to attend from (same for the whole workgroup)
+    if (a.last_row && own == 0) continue;   // no own row to attend from (same for all waves of the item)
     // keys: the prompt, the earlier generated tokens, this token (last-row
     // mode: the prompt, whose last row is the query)
     const int N = a.last_row ? P : P + a.step + 1;
     const uint16_t* qrow = !a.last_row ? qkv + i * ld : (qkv ? qkv + i * a.ldq : kvc + (s0 + own - 1) * ld);
     const int kc = d_q + kvh * HD, vc = d_q + d_kv + kvh * HD;   // key / value columns of a q|k|v row
     uint16_t* gslot = a.last_row ? nullptr : gkv + (i * a.gen + a.step) * (2 * d_kv);
-    if (!a.last_row && w == 0 && lane < 2 * LPK) {
+    if (!a.last_row && (alone || w == 0) && lane < 2 * LPK) {
       const bool isv = lane >= LPK;
       const int cc = lane % LPK;
       *reinterpret_cast<uint4*>(gslot + (isv ? d_kv : 0) + kvh * HD + cc * 8) =
@@ -210,109 +236,123 @@ __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
       }
     };
 
-    float m[REP], l[REP], o[REP][8];
-#pragma unroll
-    for (int r = 0; r < REP; ++r) {
-      m[r] = -INFINITY;
-      l[r] = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[r][e] = 0.f;
-    }
-    for (int kb = w * KB; kb < N; kb += NW * KB) {
-      uint4 kr[IT], vr[IT];
-      load_block(kb, kr, vr);
-      float s[REP][IT];
-#pragma unroll
-      for (int it = 0; it < IT; ++it) {
-        const uint32_t uw[4] = {kr[it].x, kr[it].y, kr[it].z, kr[it].w};
-        float kf[8];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          kf[2 * e] = h2f(static_cast<uint16_t>(uw[e] & 0xFFFFu));
-          kf[2 * e + 1] = h2f(static_cast<uint16_t>(uw[e] >> 16));
-        }
-        const bool ok = kb + it * KPI + gk < N;
-#pragma unroll
-        for (int r = 0; r < REP; ++r) {
-          float dot = 0.f;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) dot = fmaf(qf[r][e], kf[e], dot);
-          dot = dpp_add(dot, LPK);
-          s[r][it] = ok ? dot : -INFINITY;
-        }
-      }
-      float vf[IT][8];
-#pragma unroll
-      for (int it = 0; it < IT; ++it) {
-        const uint32_t uw[4] = {vr[it].x, vr[it].y, vr[it].z, vr[it].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          vf[it][2 * e] = h2f(static_cast<uint16_t>(uw[e] & 0xFFFFu));
-          vf[it][2 * e + 1] = h2f(static_cast<uint16_t>(uw[e] >> 16));
-        }
-      }
+    const int v_end = alone ? (N > (NW - 1) * KB ? NW : (N + KB - 1) / KB) : w + 1;
+    for (int v = alone ? 0 : w; v < v_end; ++v) {
+      float m[REP], l[REP], o[REP][8];
 #pragma unroll
       for (int r = 0; r < REP; ++r) {
-        float mx = m[r];
+        m[r] = -INFINITY;
+        l[r] = 0.f;
 #pragma unroll
-        for (int it = 0; it < IT; ++it) mx = fmaxf(mx, s[r][it]);
-        const float ref = mx == -INFINITY ? 0.f : mx;   // no key of this group yet: every term below is 0
-        const float alpha = __builtin_amdgcn_exp2f(m[r] - ref);
-        float p[IT], ps = 0.f;
+        for (int e = 0; e < 8; ++e) o[r][e] = 0.f;
+      }
+      for (int kb = v * KB; kb < N; kb += NW * KB) {
+        uint4 kr[IT], vr[IT];
+        load_block(kb, kr, vr);
+        float s[REP][IT];
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-          p[it] = __builtin_amdgcn_exp2f(s[r][it] - ref);   // 0 for keys past the end (score -inf)
-          ps += p[it];
-        }
-        l[r] = l[r] * alpha + ps;
+          const uint32_t uw[4] = {kr[it].x, kr[it].y, kr[it].z, kr[it].w};
+          float kf[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          float acc = o[r][e] * alpha;
+          for (int e = 0; e < 4; ++e) {
+            kf[2 * e] = h2f(static_cast<uint16_t>(uw[e] & 0xFFFFu));
+            kf[2 * e + 1] = h2f(static_cast<uint16_t>(uw[e] >> 16));
+          }
+          const bool ok = kb + it * KPI + gk < N;
 #pragma unroll
-          for (int it = 0; it < IT; ++it) acc = fmaf(p[it], vf[it][e], acc);
-          o[r][e] = acc;
+          for (int r = 0; r < REP; ++r) {
+            float dot = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dot = fmaf(qf[r][e], kf[e], dot);
+            dot = dpp_add(dot, LPK);
+            s[r][it] = ok ? dot : -INFINITY;
+          }
         }
-        m[r] = mx;
+        float vf[IT][8];
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+          const uint32_t uw[4] = {vr[it].x, vr[it].y, vr[it].z, vr[it].w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            vf[it][2 * e] = h2f(static_cast<uint16_t>(uw[e] & 0xFFFFu));
+            vf[it][2 * e + 1] = h2f(static_cast<uint16_t>(uw[e] >> 16));
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < REP; ++r) {
+          float mx = m[r];
+#pragma unroll
+          for (int it = 0; it < IT; ++it) mx = fmaxf(mx, s[r][it]);
+          const float ref = mx == -INFINITY ? 0.f : mx;   // no key of this group yet: every term below is 0
+          const float alpha = __builtin_amdgcn_exp2f(m[r] - ref);
+          float p[IT], ps = 0.f;
+#pragma unroll
+          for (int it = 0; it < IT; ++it) {
+            p[it] = __builtin_amdgcn_exp2f(s[r][it] - ref);   // 0 for keys past the end (score -inf)
+            ps += p[it];
+          }
+          l[r] = l[r] * alpha + ps;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            float acc = o[r][e] * alpha;
+#pragma unroll
+            for (int it = 0; it < IT; ++it) acc = fmaf(p[it], vf[it][e], acc);
+            o[r][e] = acc;
+          }
+          m[r] = mx;
+        }
+      }
+      // the key groups of the wave (then the shares: key 0 makes one maximum finite)
+      auto add = [](float x, float y) { return x + y; };
+      auto max2 = [](float x, float y) { return fmaxf(x, y); };
+#pragma unroll
+      for (int r = 0; r < REP; ++r) {
+        const float mw = across_groups<LPK>(m[r], max2);
+        const float f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[r] - mw);
+        const float lw = across_groups<LPK>(l[r] * f, add);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[r][e] = across_groups<LPK>(o[r][e] * f, add);
+        if (gk == 0) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) so[v][r][c * 8 + e] = o[r][e];
+          if (c == 0) {
+            sm[v][r] = mw;
+            sl[v][r] = lw;
+          }
+        }
       }
     }
-    // the key groups of the wave, then the waves (key 0 makes one maximum finite)
-    auto add = [](float x, float y) { return x + y; };
-    auto max2 = [](float x, float y) { return fmaxf(x, y); };
+    sync();
+    auto merge = [&](auto all, int shares, int first, int step) {   // two output values per thread
+      for (int j = first; j < REP * HD / 2; j += step) {
+        const int r = j / (HD / 2), e = (j % (HD / 2)) * 2;
+        float mm = sm[0][r], ls = 0.f, o0 = 0.f, o1 = 0.f;
+        auto take = [&](int v) {
+          const float f = __builtin_amdgcn_exp2f(sm[v][r] - mm);   // 0 for a share without keys
+          ls = fmaf(sl[v][r], f, ls);
+          o0 = fmaf(so[v][r][e], f, o0);
+          o1 = fmaf(so[v][r][e + 1], f, o1);
+        };
+        if (decltype(all)::value) {
 #pragma unroll
-    for (int r = 0; r < REP; ++r) {
-      const float mw = across_groups<LPK>(m[r], max2);
-      const float f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[r] - mw);
-      const float lw = across_groups<LPK>(l[r] * f, add);
+          for (int v = 1; v < NW; ++v) mm = fmaxf(mm, sm[v][r]);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[r][e] = across_groups<LPK>(o[r][e] * f, add);
-      if (gk == 0) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) so[w][r][c * 8 + e] = o[r][e];
-        if (c == 0) {
-          sm[w][r] = mw;
-          sl[w][r] = lw;
+          for (int v = 0; v < NW; ++v) take(v);
+        } else {
+          for (int v = 1; v < shares; ++v) mm = fmaxf(mm, sm[v][r]);
+          for (int v = 0; v < shares; ++v) take(v);
         }
+        const float inv = 1.0f / ls;
+        *reinterpret_cast<uint32_t*>(out + i * d_q + (kvh * REP + r) * HD + e) =
+            f2act(o0 * inv, a.out_act) | (static_cast<uint32_t>(f2act(o1 * inv, a.out_act)) << 16);
       }
-    }
-    __syncthreads();
-    for (int j = threadIdx.x; j < REP * HD / 2; j += 256) {   // two output values per thread
-      const int r = j / (HD / 2), e = (j % (HD / 2)) * 2;
-      float mm = sm[0][r];
-#pragma unroll
-      for (int v = 1; v < NW; ++v) mm = fmaxf(mm, sm[v][r]);
-      float ls = 0.f, o0 = 0.f, o1 = 0.f;
-#pragma unroll
-      for (int v = 0; v < NW; ++v) {
-        const float f = __builtin_amdgcn_exp2f(sm[v][r] - mm);   // 0 for a wave without keys
-        ls = fmaf(sl[v][r], f, ls);
-        o0 = fmaf(so[v][r][e], f, o0);
-        o1 = fmaf(so[v][r][e + 1], f, o1);
-      }
-      const float inv = 1.0f / ls;
-      *reinterpret_cast<uint32_t*>(out + i * d_q + (kvh * REP + r) * HD + e) =
-          f2act(o0 * inv, a.out_act) | (static_cast<uint32_t>(f2act(o1 * inv, a.out_act)) << 16);
-    }
-    __syncthreads();   // the partial states are read before the next item writes them
+    };
+    if (alone)
+      merge(std::false_type{}, v_end, lane, 64);   // shares without keys add nothing
+    else
+      merge(std::true_type{}, NW, static_cast<int>(threadIdx.x), 64 * NW);
+    sync();   // the partial states are read before the next item writes them
   }
 }
 
