@@ -377,7 +377,7 @@ struct PrefixUse {
 };
 
 // Enqueues embedding, the layer stack and the label head for one chunk.
-aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int64_t* desc, const int64_t* cu,
+aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, int64_t* desc, const int64_t* cu,
                          int64_t* ctr, const int32_t* packed, int64_t t_cap, int64_t seq_ub, int32_t* label_out,
                          float* logits_out, void* hf_out, Tracer& tr, hipStream_t s,
                          const PrefixUse& pu = PrefixUse{}) {
@@ -541,6 +541,7 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
       aa.n_kv = m.n_kv_heads;
       aa.hd = p->hd;
       aa.seq_ub = seq_ub;
+      aa.tok_ub = t_cap;
       aa.out_act = p->act;
       if (last && prune) {
         // blocks of R sequences: attention of each last position over its
@@ -655,7 +656,7 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, const int
     aa.hd = p->hd;
     aa.seq_ub = seq_ub;
     aa.out_act = p->act;
-    TRACED(tr, AIQ_K_ATTN, p->bf16 ? launch_attention_bf16(aa, s) : launch_attention_f32(aa, s));
+    TRACED(tr, AIQ_K_ATTN, launch_attention_f32(aa, s));
     TRACED(tr, AIQ_K_GEMM_O, gemm(EPI_STORE_F32, att, p->d_q, d, p->d_q, W.wo, nullptr, nullptr, delta, d));
     TRACED(tr, AIQ_K_NORM, launch_rmsnorm(desc, x, delta, W.ffn_norm, d, eps, h, p->act, t_cap, s));
     if (p->bf16)

@@ -22,8 +22,11 @@ enum Ctr : int {
   C_COUNT = 16
 };
 
-// chunk descriptor: int64 x 4 per chunk
-enum Desc : int { D_TOK_BEGIN = 0, D_NTOK = 1, D_SEQ_BEGIN = 2, D_NSEQ = 3, D_STRIDE = 4 };
+// chunk descriptor: int64 x 6 per chunk
+// D_ATTN_MAX, D_ATTN_SUM: key blocks that attention walks for the chunk's longest sequence and
+// for all of them, per head (0, 0 above ATTN_WORK_SEQS sequences); written by launch_embed_norm.
+enum Desc : int { D_TOK_BEGIN = 0, D_NTOK = 1, D_SEQ_BEGIN = 2, D_NSEQ = 3, D_ATTN_MAX = 4, D_ATTN_SUM = 5, D_STRIDE = 6 };
+constexpr int64_t ATTN_WORK_SEQS = 1024;
 
 struct DPred {
   const void* data;
@@ -236,7 +239,7 @@ struct LastDesc {
   int32_t blocks;   // ldesc[b] = {chunk's first token, rows, chunk's first sequence + b R, rows}
   int64_t R;
 };
-hipError_t launch_embed_norm(const int64_t* desc, const int64_t* cu, const int32_t* packed, const void* emb,
+hipError_t launch_embed_norm(int64_t* desc, const int64_t* cu, const int32_t* packed, const void* emb,
                              int32_t wdtype, int32_t d, int32_t vocab, float* x, int32_t* pos, int64_t* ctr,
                              const float* g, float eps, void* h, int32_t h_act, float* rs, int64_t t_cap,
                              hipStream_t s, int32_t pos_base = 0, LastDesc last = LastDesc{});
@@ -314,6 +317,7 @@ struct AttnArgs {
   const int64_t* cu;         // global cu_seqlens (int64)
   int32_t n_heads, n_kv, hd;
   int64_t seq_ub;            // host upper bound on sequences per chunk
+  int64_t tok_ub;            // MFMA path: host upper bound on tokens per chunk
   int32_t out_act;           // MFMA path: output element type (1 bf16, 2 fp16)
   // Shared prompt prefix (MFMA path): every sequence is read as
   // pkv[0..npre) followed by its own rows, positions counted from the

@@ -1,7 +1,7 @@
 // Causal self-attention over the packed variable-length batch, grouped K/V
 // heads (query head j reads K/V head j / (n_heads / n_kv)).
 //
-// Work items are (sequence, K/V head, head group), split by query block where
+// Work items are (sequence, K/V head, head group), or their 64-query blocks where
 // they are few, walked by a persistent grid; a workgroup holds REP of the n_heads / n_kv query heads that read one
 // K/V head (all of them when registers allow), four waves per query head, so
 // each staged key block serves all of them (its global reads happen once per
@@ -52,31 +52,25 @@ static int grid_cap(int64_t items, int cap) {
 
 
 // ======================================================================= bf16 MFMA
-constexpr int MAX_SPLIT = 16;   // most shares of an item's query blocks
+// A unit is a (sequence, K/V head, head group) item, whose 64-query blocks run one after
+// another, or with SPLIT one query block of an item: a small batch otherwise leaves
+// workgroups without an item while a long sequence's blocks are walked.
+// Query blocks are independent, so the results are the same bits.
+constexpr int ATTN_GRID = 8192;   // query heads' worth of workgroups
+// ... of a launch whose items are split: about what runs at once (400 sequences of 16 to 500 tokens, 8 heads of
+// 64: 45 us, 63 with the whole grid); with three 128-dim heads, one workgroup per CU,
+// the whole grid, for the dispatch to balance (30 sequences of 16 to 700: 62 us, 89 with 341).
+constexpr int split_grid(int hd, int hpw) { return (hd == 128 && hpw == 3 ? ATTN_GRID : 1024) / hpw; }
 
-template <int HD, int REP>
-__global__ __launch_bounds__(256 * REP) void k_attn_bf16(AttnArgs a) {
+template <int HD, int REP, bool SPLIT>
+__device__ __forceinline__ void attn_units(const AttnArgs& a, uint16_t* Ks, uint16_t* Vs) {
   constexpr int KB = 64;            // keys per block
   constexpr int CH = HD / 8;        // 16-byte chunks per K row
   constexpr int NT = 256 * REP;     // threads: four waves per query head of the group
   constexpr int PER = (KB * CH + NT - 1) / NT;   // chunks of K (and of V) per thread per block (at most)
-  // K and V of one key block, row-major, 16-byte chunks XOR-swizzled by row
-  // bits (K: rows 2i and 2i+1 share a pattern, so the 16 rows of a fragment
-  // read hit distinct banks; V: the rows of a transposed read do)
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[KB * HD];
-  __shared__ __attribute__((aligned(16))) uint16_t Vs[KB * HD];
-
   lds_u16* const vs_lds = (lds_u16*)(Vs);   // LDS address space, for the transposing reads
   const int64_t tb = a.desc[D_TOK_BEGIN], sb = a.desc[D_SEQ_BEGIN], ns = a.desc[D_NSEQ];
-  const int groups = a.n_heads / (a.n_kv * REP);   // head groups per K/V head
-  const int64_t n_items = ns * a.n_kv * groups;
-  // Few items (a small batch) leave workgroups without one while a long
-  // sequence's query blocks run one after another (8 sequences of up to 560
-  // tokens, 64 items: 149 us, 51 us split): a unit is then one of `split`
-  // interleaved shares of an item's query blocks.  Query blocks are
-  // independent, so the results are the same bits.
-  const int split = n_items * 2 > gridDim.x ? 1 : static_cast<int>(n_items * MAX_SPLIT > gridDim.x ? gridDim.x / n_items : MAX_SPLIT);
-  const int64_t n_units = n_items * split;
+  const uint32_t per_seq = a.n_heads / REP;   // K/V heads times head groups of each
   const int t = threadIdx.x, lane = t & 63, g = lane >> 4, c16 = lane & 15;
   const int w = (t >> 6) & 3;      // the wave's 16 queries of a 64-query block
   const int hq = t >> 8;           // its query head inside the workgroup's group
@@ -92,22 +86,77 @@ __global__ __launch_bounds__(256 * REP) void k_attn_bf16(AttnArgs a) {
   // key block and the queries of the next task are read while the last key
   // block of the current one is consumed.
   struct Task {
-    int64_t unit, s0;   // unit, first packed row of the sequence's own rows
+    int64_t s0;          // first packed row of the sequence's own rows
+    uint32_t unit;
     int L, qb, h0;       // positions (prefix + own), query block, first query head of the group
   };
+  // SPLIT: the sequences before seq0 hold blk0 query blocks (units ascend, so the
+  // search for a unit's sequence goes on where the last one ended)
+  uint32_t seq0 = 0, blk0 = 0;
+  const uint32_t grid = SPLIT && gridDim.x > split_grid(HD, REP) ? split_grid(HD, REP) : gridDim.x;
   // first task of the first unit at or after `unit` that has one
-  auto unit_task = [&](int64_t unit, Task& tk) -> bool {
-    for (; unit < n_units; unit += gridDim.x) {
-      const int per_seq = a.n_kv * groups;
-      const int32_t item = static_cast<int32_t>(unit) / split;   // units < 2^31 (checked at launch)
-      const int64_t si = item / per_seq;
-      const int64_t c0 = a.cu[sb + si], c1 = a.cu[sb + si + 1];
-      tk.L = static_cast<int>(c1 - c0) + np;
-      tk.qb = np / KB + (static_cast<int32_t>(unit) - item * split);
-      if (c1 > c0 && tk.qb * KB < tk.L) {
-        const int r = static_cast<int>(item - si * per_seq);   // K/V head r / groups, group r % groups
+  auto unit_task = [&](uint32_t unit, Task& tk) -> bool {
+    if (SPLIT) {
+      // unit: query block b of the chunk's (sequences in order), K/V head and group r
+      // round k of the grid starts k query blocks on: sequences of equal length do not
+      // give a workgroup the same block of each
+      uint32_t to = unit;
+      if (unit >= grid) {
+        const uint32_t k = unit / grid;
+        to = (unit + k * per_seq) % grid + k * grid;
+      }
+      const uint32_t b = to / per_seq, r = to - b * per_seq;
+      // no sequence has more than own / 64 + 1 query blocks (+ 2 behind an unaligned prefix)
+      if (b >= static_cast<uint64_t>(a.desc[D_NTOK] / KB + ns * (np % KB ? 2 : 1))) return false;
+      if (ns == 1) {
+        const int64_t c0 = a.cu[sb], c1 = a.cu[sb + 1];
         tk.unit = unit;
         tk.s0 = c0 - tb;
+        tk.L = static_cast<int>(c1 - c0) + np;
+        tk.qb = np / KB + static_cast<int>(b);
+        tk.h0 = static_cast<int>(r) * REP;
+        return c1 > c0 && tk.qb * KB < tk.L;
+      }
+      for (; seq0 < ns; seq0 += 64) {   // 64 sequences at a time, one per lane
+        int64_t c0 = 0;
+        int own = 0, nb = 0;
+        if (seq0 + lane < ns) {
+          c0 = a.cu[sb + seq0 + lane];
+          own = static_cast<int>(a.cu[sb + seq0 + lane + 1] - c0);
+          nb = own > 0 ? (np + own + KB - 1) / KB - np / KB : 0;
+        }
+        int incl = nb;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int v = __shfl_up(incl, o);
+          if (lane >= o) incl += v;
+        }
+        const uint64_t past = __ballot(static_cast<uint32_t>(incl) > b - blk0);
+        if (past) {
+          const int l = __ffsll(static_cast<unsigned long long>(past)) - 1;
+          tk.unit = unit;
+          tk.s0 = (static_cast<int64_t>(__builtin_amdgcn_readlane(static_cast<int>(c0 >> 32), l)) << 32 |
+                   static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(c0), l))) - tb;
+          tk.L = __builtin_amdgcn_readlane(own, l) + np;
+          tk.qb = np / KB + static_cast<int>(b - blk0) -
+                  (__builtin_amdgcn_readlane(incl, l) - __builtin_amdgcn_readlane(nb, l));
+          tk.h0 = static_cast<int>(r) * REP;
+          return true;
+        }
+        blk0 += __builtin_amdgcn_readlane(incl, 63);
+      }
+      return false;
+    }
+    const uint32_t n_units = static_cast<uint32_t>(ns) * per_seq;   // < 2^31 (checked at launch)
+    for (; unit < n_units; unit += grid) {
+      const uint32_t si = unit / per_seq;
+      const int64_t c0 = a.cu[sb + si], c1 = a.cu[sb + si + 1];
+      if (c1 > c0) {
+        const int r = static_cast<int>(unit - si * per_seq);   // K/V head r / groups, group r % groups
+        tk.unit = unit;
+        tk.s0 = c0 - tb;
+        tk.L = static_cast<int>(c1 - c0) + np;
+        tk.qb = np / KB;
         tk.h0 = r * REP;   // K/V head r / groups owns query heads (r / groups) * rep ..
         return true;
       }
@@ -115,12 +164,12 @@ __global__ __launch_bounds__(256 * REP) void k_attn_bf16(AttnArgs a) {
     return false;
   };
   auto advance = [&](const Task& c, Task& n) -> bool {
-    if ((c.qb + split) * KB < c.L) {
+    if (!SPLIT && (c.qb + 1) * KB < c.L) {
       n = c;
-      n.qb = c.qb + split;
+      n.qb = c.qb + 1;
       return true;
     }
-    return unit_task(c.unit + gridDim.x, n);
+    return unit_task(c.unit + grid, n);
   };
   // row of position p: the prefix's rows, then the sequence's own rows
   auto row_of = [&](const Task& tk, int p) {
@@ -159,7 +208,7 @@ __global__ __launch_bounds__(256 * REP) void k_attn_bf16(AttnArgs a) {
   };
 
   Task cur;
-  if (!unit_task(blockIdx.x, cur)) return;
+  if (blockIdx.x >= grid || !unit_task(blockIdx.x, cur)) return;
   half8 qf[HD / 32];
   load_q(cur, qf);
   fetch(cur, 0);
@@ -316,6 +365,31 @@ __global__ __launch_bounds__(256 * REP) void k_attn_bf16(AttnArgs a) {
   }
 }
 
+// Waves per SIMD that the registers leave room for, so that both forms in one kernel do not
+// cost one.  (One 128-dim head is faster with its accumulators in the other half of the register file.)
+constexpr int attn_waves(int hd, int hpw) { return hd == 64 ? 4 : (hpw == 1 ? 1 : 3); }
+
+template <int HD, int REP>
+__global__ __launch_bounds__(256 * REP, attn_waves(HD, REP)) void k_attn_bf16(AttnArgs a) {
+  // K and V of one key block, row-major, 16-byte chunks XOR-swizzled by row
+  // bits (K: rows 2i and 2i+1 share a pattern, so the 16 rows of a fragment
+  // read hit distinct banks; V: the rows of a transposed read do)
+  __shared__ __attribute__((aligned(16))) uint16_t Ks[64 * HD];
+  __shared__ __attribute__((aligned(16))) uint16_t Vs[64 * HD];
+  // Items are split where the longest one exceeds twice the work (key blocks) that each of the
+  // `slots` workgroups running at once would get: the chip waits for it otherwise.  Where items
+  // keep the chip busy, walking an item's blocks with the next one's loads in flight is
+  // faster.  Unsplit and split, heads of 64 in groups of 1: one sequence of 3,000 tokens 1,182 and 57 us, 100
+  // of 16 to 500 50 and 21, 20 of 300 25 and 15, but 60 of 200 22 and 24, 60 of 300 30 and 32 (groups of 3,
+  // heads of 128: 122 and 166).
+  constexpr int slots = 256 * (attn_waves(HD, REP) / REP > 1 ? attn_waves(HD, REP) / REP : 1);
+  const bool split = a.desc[D_ATTN_MAX] * slots > 2 * a.desc[D_ATTN_SUM] * (a.n_heads / REP);
+  if (!split)
+    attn_units<HD, REP, false>(a, Ks, Vs);
+  else
+    attn_units<HD, REP, true>(a, Ks, Vs);
+}
+
 hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s) {
   if (a.npre < 0 || (a.npre > 0 && !a.pkv)) return hipErrorInvalidValue;
   if (a.n_kv <= 0 || a.n_heads % a.n_kv) return hipErrorInvalidValue;
@@ -331,7 +405,10 @@ hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s) {
   // about 32 query heads' worth of workgroups per CU: with work items of very
   // unequal length (sequence lengths spread 16..512) a fine grid balances the
   // tail better
-  const int g = grid_cap(items * MAX_SPLIT, 8192 / hpw);
+  // (or all query blocks', where items are split)
+  int64_t blocks = (a.tok_ub / 64 + a.seq_ub * (a.npre % 64 ? 2 : 1)) * (a.n_heads / hpw);
+  if (blocks > split_grid(a.hd, hpw)) blocks = split_grid(a.hd, hpw);
+  const int g = grid_cap(items > blocks ? items : blocks, ATTN_GRID / hpw);
 #define AIQ_ATTN(HD, R) hipLaunchKernelGGL((k_attn_bf16<HD, R>), dim3(g), dim3(256 * R), 0, s, a)
   if (a.hd == 64) {
     switch (hpw) {

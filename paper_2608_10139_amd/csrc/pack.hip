@@ -288,7 +288,7 @@ __global__ __launch_bounds__(256) void k_embed(const int64_t* desc, const int64_
 constexpr int EMB_RUN = 4;
 
 template <bool F16>
-__global__ __launch_bounds__(256) void k_embed_norm(const int64_t* desc, const int64_t* cu, const int32_t* packed,
+__global__ __launch_bounds__(256) void k_embed_norm(int64_t* desc, const int64_t* cu, const int32_t* packed,
                                                     const uint16_t* emb, int32_t d, int32_t vocab, float* x,
                                                     int32_t* pos, int64_t* ctr, const float* g, float eps, uint16_t* h,
                                                     float* rs, int32_t pos_base, LastDesc last) {
@@ -305,6 +305,25 @@ __global__ __launch_bounds__(256) void k_embed_norm(const int64_t* desc, const i
       o[D_NSEQ] = r;
     }
   const int lane = threadIdx.x & 63;
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 64) {   // what attention walks per sequence: own blocks of 64 queries,
+    int64_t most = 0, sum = 0;                             // each against the key blocks up to its own
+#pragma unroll 4
+    for (int64_t i = lane; i < ns && ns <= ATTN_WORK_SEQS; i += 64) {
+      const int64_t nb = (cu[sb + i + 1] - cu[sb + i] + 63) / 64, work = nb * (nb + 1) / 2 + nb * (pos_base / 64);
+      if (work > most) most = work;
+      sum += work;
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t v = __shfl_xor(most, o);
+      if (v > most) most = v;
+      sum += __shfl_xor(sum, o);
+    }
+    if (lane == 0) {
+      desc[D_ATTN_MAX] = most;
+      desc[D_ATTN_SUM] = sum;
+    }
+  }
   const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
   for (int64_t t0 = wave * EMB_RUN; t0 < nt; t0 += n_waves * EMB_RUN) {
@@ -386,7 +405,7 @@ hipError_t launch_embed(const int64_t* desc, const int64_t* cu, const int32_t* p
   return hipGetLastError();
 }
 
-hipError_t launch_embed_norm(const int64_t* desc, const int64_t* cu, const int32_t* packed, const void* emb,
+hipError_t launch_embed_norm(int64_t* desc, const int64_t* cu, const int32_t* packed, const void* emb,
                              int32_t wdtype, int32_t d, int32_t vocab, float* x, int32_t* pos, int64_t* ctr,
                              const float* g, float eps, void* h, int32_t h_act, float* rs, int64_t t_cap,
                              hipStream_t s, int32_t pos_base, LastDesc last) {
