@@ -530,12 +530,12 @@ __device__ __forceinline__ uint32_t lds_offset(const void* p) {
 }
 __device__ __forceinline__ void dma_global(const void* src, uint32_t dst) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src)
-               : "memory");
+               : "memory", "m0");
 }
 __device__ __forceinline__ void dma_buffer(int __attribute__((ext_vector_type(4))) rsrc, int voff, int soff, uint32_t dst) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(voff),
                "s"(rsrc), "s"(soff)
-               : "memory");
+               : "memory", "m0");
 }
 
 // 16-byte chunk c of row r of the finished tile in LDS.
