@@ -191,6 +191,17 @@ void take_resid(const aiq_plan* p, Carver& c, Layout& L, size_t T) {
   L.pos = c.take((T + 256) * 4);   // GEMM tiles read positions up to the tile edge
 }
 
+// rotary frequencies (MFMA path), or cos / sin of every position (fp32 path)
+void take_rope(const aiq_plan* p, Carver& c, Layout& L, size_t positions) {
+  const size_t half = static_cast<size_t>(p->hd / 2) * 4;
+  if (p->bf16) {
+    L.rrev = c.take(half);
+  } else {
+    L.rcos = c.take(positions * half);
+    L.rsin = c.take(positions * half);
+  }
+}
+
 // Last positions of a chunk go through the pruned last layer in blocks of at
 // most LAST_ROWS_MAX sequences (their fp32 residual rows: 3 GB at d 3072).
 // Every block is launched for every chunk pass, also where the selection
@@ -260,9 +271,7 @@ Layout run_layout(const aiq_plan* p) {
     L.gn = c.take(8);
   }
   L.desc = c.take(static_cast<size_t>(p->n_chunks) * D_STRIDE * 8);
-  L.rcos = c.take(static_cast<size_t>(p->max_seq) * (p->hd / 2) * 4);
-  L.rsin = c.take(static_cast<size_t>(p->max_seq) * (p->hd / 2) * 4);
-  L.rrev = c.take(static_cast<size_t>(p->hd / 2) * 4);
+  take_rope(p, c, L, static_cast<size_t>(p->max_seq));
   take_resid(p, c, L, static_cast<size_t>(p->t_cap));
   take_last(p, c, L, p->seq_ub);
   L.hf = 0;
@@ -312,9 +321,7 @@ Layout prefill_layout(const aiq_plan* p, int64_t max_tokens) {
   L.desc = c.take(D_STRIDE * 8);
   L.cu = c.take((T + 1) * 8);
   L.label = c.take((T + 1) * 4);
-  L.rcos = c.take(T * (p->hd / 2) * 4);
-  L.rsin = c.take(T * (p->hd / 2) * 4);
-  L.rrev = c.take(static_cast<size_t>(p->hd / 2) * 4);
+  take_rope(p, c, L, T);
   take_resid(p, c, L, T);
   take_last(p, c, L, static_cast<int64_t>(T));   // sequences <= tokens
   L.hf = c.take(T * d * ab);
@@ -418,8 +425,6 @@ aiq_status enqueue_chunk(const aiq_plan* p, void* ws, const Layout& L, int64_t* 
     g.C = C;
     g.ldc = ldc;
     g.pos = pos;
-    g.rope_cos = rcos;
-    g.rope_sin = rsin;
     g.rope_rev = rrev;
     g.f16 = p->act == 2;
     g.rs = rs;

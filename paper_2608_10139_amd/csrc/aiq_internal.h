@@ -279,8 +279,6 @@ struct GemmArgs {
   void* C;                   // output
   int64_t ldc;
   const int32_t* pos;        // [M + 256] positions (EPI_QKV_ROPE; entries past M are ignored)
-  const float* rope_cos;     // [max_pos, hd/2] (fp32 path)
-  const float* rope_sin;
   const float* rope_rev;     // [hd/2] theta^(-2i/hd) / (2 pi) (MFMA path)
   int32_t f16;               // MFMA path: operands are fp16 (else bf16)
   // Residual stream with the RMSNorm folded into the projections (MFMA path):

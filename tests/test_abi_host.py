@@ -70,6 +70,20 @@ def query(**kw):
     return q
 
 
+def test_16_bit_models_reserve_no_rotary_tables():
+    """Their projections take the angles from the frequencies of a head's dims; the
+    cos / sin tables (8 bytes per position and pair of dims) belong to the fp32
+    path.  Heads of 64 and of 128 with the same widths need the same workspace
+    (but for the frequencies, one 256-byte block either way)."""
+    plans = [B.aiq_plan_create(model(n_heads=h, n_kv_heads=h), table(), None, query()) for h in (8, 4)]
+    try:
+        for size in (B.aiq_workspace_size, lambda p: B.aiq_prefill_workspace_size(p, 4096)):
+            assert size(plans[0]) == size(plans[1])
+    finally:
+        for p in plans:
+            B.aiq_plan_destroy(p)
+
+
 def test_valid_plan_and_workspace_size():
     p = B.aiq_plan_create(model(), table(), None, query())
     try:
