@@ -24,9 +24,9 @@ enum Ctr : int {
 
 // chunk descriptor: int64 x 6 per chunk
 // D_ATTN_MAX, D_ATTN_SUM: key blocks that attention walks for the chunk's longest sequence and
-// for all of them, per head (0, 0 above ATTN_WORK_SEQS sequences); written by launch_embed_norm.
+// for all of them, per head (0, 0 above ATTN_WORK_SEQS sequences); written by launch_embed_norm (MFMA path).
 enum Desc : int { D_TOK_BEGIN = 0, D_NTOK = 1, D_SEQ_BEGIN = 2, D_NSEQ = 3, D_ATTN_MAX = 4, D_ATTN_SUM = 5, D_STRIDE = 6 };
-constexpr int64_t ATTN_WORK_SEQS = 1024;
+constexpr int64_t ATTN_WORK_SEQS = 4096;
 
 struct DPred {
   const void* data;
@@ -412,7 +412,7 @@ struct GenAttnArgs {
   int32_t step, gen;
   int64_t ld;
   const int64_t* gen_desc;
-  const int64_t* chunk_desc; // for the chunk's first token
+  const int64_t* chunk_desc; // for the chunk's first token and its longest sequence
   const int64_t* cu;
   void* out;                 // [n, n_heads * hd]
   int32_t n_heads, n_kv, hd, out_act;

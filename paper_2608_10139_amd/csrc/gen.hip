@@ -129,14 +129,20 @@ __device__ __forceinline__ float across_groups(float v, F f) {
 }
 
 // Items from which on waves take them alone (groups of up to 3; wider ones keep a wave busy
-// with registers).  8 heads of 64, alone against a workgroup per item: 800 items of 8 / 40 / 170
-// keys 3.8 / 5.2 / 11.7 us against 4.4 / 5.3 / 9.9; 2,000 items 4.2 / 7.6 / 17.1 against
-// 7.4 / 9.2 / 17.5; 160,000 items of 2 / 33 keys 106 / 292 against 323 / 452.
-// Groups of 3, heads of 128: 2,000 items 9.1 / 16.7 / 41.8 against 14.2 / 18.0 / 45.7.
-constexpr int64_t GEN_ALONE_ITEMS = 2000;
+// with registers): where they fill the chip several times over, and earlier where the longest
+// prompt is short, since a long one is then a wave's serial chain.  A workgroup per item against
+// waves alone, 8 K/V heads of 64: 2,000 sequences of 16 to 100 tokens 41 and 19 us, of 16 to
+// 500 70 and 59, 1,000 22 and 13, 31 and 32, 500 13 and 10, 18 and 26, 250 7.3 and 8.0; 20,000 of
+// two tokens 312 and 106.  Groups of 3, heads of 128: 2,000 89 and 53, 138 and 140, 500 26 and 26, 52
+// and 79.
+constexpr int64_t GEN_ALONE_ITEMS = 16000, GEN_ALONE_SHORT = 4000;
+constexpr int GEN_SHORT_WORK = 3;   // D_ATTN_MAX of two blocks of 64 positions
+
+// waves per SIMD that the registers leave room for
+constexpr int gen_waves(int hd, int rep) { return rep <= 3 ? 7 - rep : rep == 4 ? (hd == 64 ? 4 : 3) : 2; }
 
 template <int HD, int REP>
-__global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
+__global__ __launch_bounds__(256, gen_waves(HD, REP)) void k_attn_gen(GenAttnArgs a) {
   constexpr int LPK = HD / 8;     // lanes per key row
   constexpr int KPI = 64 / LPK;   // key rows per wave load
   constexpr int IT = 4;           // wave loads per block
@@ -157,7 +163,8 @@ __global__ __launch_bounds__(256) void k_attn_gen(GenAttnArgs a) {
   const int64_t items = n * a.n_kv;
   // Where items are many, each wave takes items by itself, their shares one
   // after another: the same sums without waiting for the other waves.
-  const bool alone = ALONE && items >= GEN_ALONE_ITEMS;
+  const bool is_short = a.chunk_desc[D_ATTN_MAX] > 0 && a.chunk_desc[D_ATTN_MAX] <= GEN_SHORT_WORK && a.step < 64;
+  const bool alone = ALONE && items >= (is_short ? GEN_ALONE_SHORT : GEN_ALONE_ITEMS);
   const int per_wg = alone ? NW : 1;
   float (*const so)[REP][HD] = so_ + (alone ? NW * w : 0);
   float (*const sm)[REP] = sm_ + (alone ? NW * w : 0);

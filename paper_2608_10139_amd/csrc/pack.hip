@@ -305,10 +305,11 @@ __global__ __launch_bounds__(256) void k_embed_norm(int64_t* desc, const int64_t
       o[D_NSEQ] = r;
     }
   const int lane = threadIdx.x & 63;
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 64) {   // what attention walks per sequence: own blocks of 64 queries,
-    int64_t most = 0, sum = 0;                             // each against the key blocks up to its own
+  if (blockIdx.x == gridDim.x - 1) {   // a block of its own: what attention walks per sequence, own
+    __shared__ int64_t part[2][4];     // blocks of 64 queries, each against the key blocks up to its own
+    int64_t most = 0, sum = 0;
 #pragma unroll 4
-    for (int64_t i = lane; i < ns && ns <= ATTN_WORK_SEQS; i += 64) {
+    for (int64_t i = threadIdx.x; i < ns && ns <= ATTN_WORK_SEQS; i += 256) {
       const int64_t nb = (cu[sb + i + 1] - cu[sb + i] + 63) / 64, work = nb * (nb + 1) / 2 + nb * (pos_base / 64);
       if (work > most) most = work;
       sum += work;
@@ -320,12 +321,22 @@ __global__ __launch_bounds__(256) void k_embed_norm(int64_t* desc, const int64_t
       sum += __shfl_xor(sum, o);
     }
     if (lane == 0) {
+      part[0][threadIdx.x >> 6] = most;
+      part[1][threadIdx.x >> 6] = sum;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int v = 1; v < 4; ++v) {
+        if (part[0][v] > most) most = part[0][v];
+        sum += part[1][v];
+      }
       desc[D_ATTN_MAX] = most;
       desc[D_ATTN_SUM] = sum;
     }
+    return;
   }
   const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  const int64_t n_waves = ((int64_t)(gridDim.x - 1) * blockDim.x) >> 6;
   for (int64_t t0 = wave * EMB_RUN; t0 < nt; t0 += n_waves * EMB_RUN) {
     const int n = nt - t0 < EMB_RUN ? static_cast<int>(nt - t0) : EMB_RUN;
     // lane u < n: token t0 + u and its position
@@ -411,7 +422,7 @@ hipError_t launch_embed_norm(int64_t* desc, const int64_t* cu, const int32_t* pa
                              hipStream_t s, int32_t pos_base, LastDesc last) {
   if (d % 8 || h_act != (wdtype == AIQ_F16 ? ACT_F16 : ACT_BF16) || (wdtype != AIQ_F16 && wdtype != AIQ_BF16))
     return hipErrorInvalidValue;
-  const dim3 grid(grid_for(t_cap, 4 * EMB_RUN, 8192));
+  const dim3 grid(grid_for(t_cap, 4 * EMB_RUN, 8192) + 1);
   if (wdtype == AIQ_F16)
     hipLaunchKernelGGL(k_embed_norm<true>, grid, dim3(256), 0, s, desc, cu, packed, static_cast<const uint16_t*>(emb), d,
                        vocab, x, pos, ctr, g, eps, static_cast<uint16_t*>(h), rs, pos_base, last);

@@ -3,8 +3,8 @@ one sequence to several workgroups where one sequence outweighs the rest, waves
 that take last-position items alone where there are many, as many waves per head
 row as its width fills.  A row's logits must not depend on which of them ran: rows
 at the edges of the query and key blocks (rows without tokens between them, more
-than the 64 that are searched at a time) alone, in a batch of 80 and among 3,000
-others give the same bits, with and without a shared prefix, and the fp64 oracle's
+than the 64 that are searched at a time) alone, in a batch of 80 and among 9,000
+others (the short ones among 2,200) give the same bits, with and without a shared prefix, and the fp64 oracle's
 values.  The norm gains are random, so that a gain read at a wrong place shows."""
 import numpy as np
 import pytest
@@ -54,9 +54,12 @@ def test_row_bits_do_not_depend_on_the_batch(heads, npre):
     rows = [r.integers(3, 1024, n).astype(np.int32) for n in lens]
     print("  batch of 80", flush=True)
     got = run(rows, prefix, m, dm, npre)
-    print("  among 3,000 others", flush=True)
-    others = [r.integers(3, 1024, n).astype(np.int32) for n in r.integers(0, 60, 3000)]
+    others = [r.integers(3, 1024, n).astype(np.int32) for n in r.integers(0, 60, 9000)]
+    print("  among 9,000 others", flush=True)
     assert np.array_equal(run(rows + others, prefix, m, dm, npre)[:80], got)
+    short = [i for i, n in enumerate(lens) if n <= 64]
+    print("  short rows among 2,200 others", flush=True)
+    assert np.array_equal(run([rows[i] for i in short] + others[:2200], prefix, m, dm, npre)[:len(short)], got[short])
     for n in (1, 33, 65, 129, 700):
         i = lens.index(n)
         print("  alone:", n, flush=True)
