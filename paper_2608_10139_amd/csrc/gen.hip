@@ -103,7 +103,7 @@ hipError_t launch_last_rows(const int64_t* ldesc, const int64_t* cu, const LastR
 // kept key and value row once), the chain of blocks for few.  One wave per
 // item with the maximum and the sum of every block reduced over the wave
 // through the LDS crossbar took 32 us per step for 256 sequences of 170 keys
-// (8 heads of 64) and 98 us for 8 sequences of up to 560 (groups of 3, heads of
+// (8 heads of 64) and 98 us for 8 sequences of up to 585 (groups of 3, heads of
 // 128); this takes 23 and 21 us.  The split depends on the keys alone, so a sequence's
 // bits do not depend on the batch.  The workgroup also stores this step's key and
 // value into the generated cache.

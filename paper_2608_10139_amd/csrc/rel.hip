@@ -770,8 +770,9 @@ __device__ __forceinline__ void look_back(int64_t* lb, int64_t* ctr, int64_t b, 
 // relational-only plan) positions need only the survivor counts: a block
 // publishes its count as soon as its masks are known and wave 0 walks back while
 // the others read the list lengths, whose sum goes to lb[4b + 3] for
-// k_finalize_rel.  With the offsets, whole relational call: 2^26 rows at 1 % 131 us,
-// 2^24 at 50 % 82, at 100 % 104; without: 124, 53, 59.  Blocks of 4,096 or 16,384
+// k_finalize_rel.  With the offsets, whole relational call, repeated on the same table: 2^26 rows
+// at 1 % 133 us, 2^24 at 50 % 82, at 100 % 105; without: 124, 53, 59 (2^24 at 50 % 62 where other
+// tables run in between: the columns are then not in the 256 MB cache).  Blocks of 4,096 or 16,384
 // rows (143 and 159 us at 2^26), look-back steps of 128 or 256 predecessors (130, 144)
 // and fewer resident blocks (the same down to three per CU) are no better.
 template <bool STAGED, bool CU>
