@@ -3,7 +3,7 @@ one sequence to several workgroups where one sequence outweighs the rest, waves
 that take last-position items alone where there are many, as many waves per head
 row as its width fills.  A row's logits must not depend on which of them ran: rows
 at the edges of the query and key blocks (rows without tokens between them, more
-than the 64 that are searched at a time) alone, in a batch of 80 and among 9,000
+than the 64 that are searched at a time) alone, in a batch of 80 and behind 3,000 and 9,000
 others (the short ones among 2,200) give the same bits, with and without a shared prefix, and the fp64 oracle's
 values.  The norm gains are random, so that a gain read at a wrong place shows."""
 import numpy as np
@@ -55,8 +55,9 @@ def test_row_bits_do_not_depend_on_the_batch(heads, npre):
     print("  batch of 80", flush=True)
     got = run(rows, prefix, m, dm, npre)
     others = [r.integers(3, 1024, n).astype(np.int32) for n in r.integers(0, 60, 9000)]
-    print("  among 9,000 others", flush=True)
-    assert np.array_equal(run(rows + others, prefix, m, dm, npre)[:80], got)
+    for n in (3000, 9000):   # 3,000: query blocks shared out among 3,080 sequences; 9,000: whole sequences
+        print("  among others:", n, flush=True)
+        assert np.array_equal(run(others[:n] + rows, prefix, m, dm, npre)[n:], got)
     short = [i for i, n in enumerate(lens) if n <= 64]
     print("  short rows among 2,200 others", flush=True)
     assert np.array_equal(run([rows[i] for i in short] + others[:2200], prefix, m, dm, npre)[:len(short)], got[short])
